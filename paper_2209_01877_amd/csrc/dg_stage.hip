@@ -60,6 +60,36 @@ constexpr int stage_min_blocks() {
   return (P <= 3 && !Pr::f64) || (P <= 2 && Pr::f64) ? 2 : 1;
 }
 
+// Wavefronts per SIMD of the split kernel (W wavefronts per group, see below): mixed P3 at
+// three (166 registers, 50 KB of LDS per workgroup), the others as the unsplit kernel.
+template <int P, class Pr, int W>
+constexpr int wave_bound() {
+  return W > 1 && Pr::mixed && P == 3 ? 3 : stage_min_blocks<P, Pr>();
+}
+
+// Wavefronts that share a group in the split kernel: one per face, and one per volume point
+// tile at P3.
+constexpr int kSplitWaves = 4;
+
+// The split kernel runs up to this many 16-element groups per two CUs; above, the unsplit
+// kernel's one group per wavefront fills the chip better.  Stage times in us, unsplit | split,
+// at 24, 648 and 1536 groups (256 CUs), Rusanov:
+//   FP64  P1 14.1 15.0 19.6 | 6.8 11.3 19.4      P2 30.0 31.8 48.1 | 11.1 23.3 40.1
+//         P3 51.3 58.0 97.9 | 18.7 52.4 101.7    P4 181 182 361    | 58.4 173 339
+//   FP32  P1 13.0 13.4 18.0 | 6.7 10.9 17.2      P2 21.7 22.5 32.2 | 9.2 17.8 29.2
+//         P3 33.1 36.8 56.4 | 13.5 28.8 51.1     P4 101 118 196    | 31.1 87.7 171
+//   fp16  P1 15.1 16.6 22.7 | 9.4 15.7 27.0      P2 16.2 18.1 26.3 | 9.7 16.5 28.5
+//         P3 18.2 22.4 33.8 | 10.1 18.6 32.6     P4 37.4 46.6 81.5 | 18.0 51.8 101
+// The line lies below the largest mesh that the unsplit kernel takes in one round of
+// wavefronts (two per SIMD: 2048 groups; one per SIMD, FP64 P3 and every P4: 1024), since its
+// time is flat up to there.
+template <int P, class Pr>
+constexpr int split_limit() {
+  if (Pr::mixed) return P == 3 ? 12 : P == 4 ? 4 : 5;
+  if (Pr::f64) return P <= 2 ? 12 : 5;
+  return P <= 3 ? 12 : 6;
+}
+
 // FP64 at P1, P2 (two waves per SIMD) and P4 (tables in global memory): the current face's
 // neighbour operands wait in LDS instead of registers.
 template <int P, class Pr>
@@ -77,8 +107,32 @@ constexpr bool stage_nbr_lds() {
 // stores alpha_w U0 + (1 - alpha_w) times the stage result and writes the result's fp64
 // cell means beside its companion.
 enum : int { kEpiRK = 0, kEpiResid = 1, kEpiRK0 = 2, kEpiRKW = 3 };
-template <int P, class Pr, bool kLds, bool kRoe, int kEpi>
-__global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel(StageArgs a) {
+
+// A workgroup's LDS array of a split kernel (a function of its own, so that the other
+// instantiations do not carry it).
+template <class X, int N, int Tag>
+__device__ __forceinline__ X* split_lds() {
+  __shared__ X a[N];
+  return a;
+}
+
+// W: wavefronts that share one 16-element group.  1: each wavefront sweeps groups of its own
+// (large meshes).  Otherwise the workgroup's W = 4 wavefronts split one group (small meshes,
+// split_limit): a mesh that leaves the chip idle is bound by the latency of one group through
+// the kernel, so wavefront w takes face w and the volume point tiles w, w + 4, ..., and after
+// a barrier the (mode tile, variable) pairs of the epilogue are dealt out over the wavefronts.
+// FP32 / FP64 exchange partial accumulators; the mixed modes exchange the packed projection
+// and lift operands instead, so that each pair's accumulation runs in the unsplit kernel's
+// order and rounds alike.  The tables are read through the caches (each wavefront needs about a
+// quarter of them, once), the epilogue's form is a uniform branch.  Two waves per group took
+// longer at every size up to the limit but one (FP64 P3, 376 groups: 32.5 against 35.1 us),
+// eight gained at most 10 % below 256 groups (mixed modes) and lost above.
+template <int P, class Pr, bool kLds, bool kRoe, int kEpi, int W = 1>
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) void stage_kernel(
+    StageArgs a) {
+  constexpr bool kSplit = W > 1;
+  static_assert(W == 1 || W == 4, "a wavefront per face");
+  constexpr int kTag = W * 2 + (kRoe ? 1 : 0);  // keeps the split kernels' LDS arrays apart
   using O = Ord<P>;
   using L = Layout<P, Pr::KW>;
   using S = typename Pr::S;
@@ -93,18 +147,18 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
   // 32 KS operand values) is followed by 8 padding values, so that the 16 columns' records
   // start in different LDS banks (a 320-byte stride put four columns on each bank group).
   constexpr int CES = 5 * 32 * KS + 8;  // record stride, operand values
-  __shared__ Op lds_comp[Pr::mixed ? 4 * 16 * CES / 8 : 1];
+  __shared__ Op lds_comp[Pr::mixed && !kSplit ? 4 * 16 * CES / 8 : 1];
   // mixed modes: per-wave exchange of the cell-mean face data.  The four lane groups of a
   // column hold the same element, so lane group g evaluates face g's mean flux, neighbour
   // mean and normal once, and every lane reads face f's record here: 7 float pairs
   // (neighbour / ghost mean 5, mean flux 5, N 3, |N| 1), pair-major so that the lanes of a
   // wave access consecutive 8-byte words
   typedef float f2v_t __attribute__((ext_vector_type(2)));
-  __shared__ f2v_t lds_face[Pr::mixed ? 7 * 4 * 64 : 1];
+  __shared__ f2v_t lds_face[Pr::mixed && !kSplit ? 7 * 4 * 64 : 1];
   // the current face's neighbour operands in LDS (FP64 at P1, P2 and P4), one slot per
   // lane (each lane reads back only what it wrote): this keeps the kernel within its
   // registers (two waves per SIMD at P1 and P2; fewer spills at P4)
-  constexpr bool kNbrLds = stage_nbr_lds<P, Pr>();
+  constexpr bool kNbrLds = !kSplit && stage_nbr_lds<P, Pr>();
   __shared__ Op lds_nbr[kNbrLds ? 4 * 5 * KS * 64 : 1];
   const Op* __restrict__ tab;
   if constexpr (kLds) {
@@ -118,7 +172,7 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
 
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
   const int wslot = threadIdx.x >> 6;  // wavefront within the workgroup
-  if constexpr (Pr::mixed) {
+  if constexpr (Pr::mixed && !kSplit) {
     // the staging records' padding (modes past the last, the slots past the last mode
     // tile) is never written by the epilogue: zero it once
     uint32_t* z = reinterpret_cast<uint32_t*>(lds_comp) + wslot * 8 * CES;
@@ -167,12 +221,14 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
   const int nwb = blockDim.x >> 6;
   const int nx = (nblk % 8 == 0) ? 8 : 1;
   const int xcd = blockIdx.x % nx;
-  const int64_t waves_x = (int64_t)(nblk / nx) * nwb;
-  const int64_t wave_x = (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);
+  const int64_t waves_x = (int64_t)(nblk / nx) * (kSplit ? 1 : nwb);
+  const int64_t wave_x = kSplit ? blockIdx.x / nx : (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);
   const int64_t ngroups = epad / 16;
   const int64_t chunk = (ngroups + nx - 1) / nx;
   const int64_t g_begin = xcd * chunk;
   const int64_t g_end = g_begin + chunk < ngroups ? g_begin + chunk : ngroups;
+  // a split wavefront's number: its first face and volume point tile, in strides of W
+  const int wu = kSplit ? __builtin_amdgcn_readfirstlane(wslot) : 0;
 
   for (int64_t grp = g_begin + wave_x; grp < g_end; grp += waves_x) {
     const int e = (int)(grp * 16 + col);
@@ -237,7 +293,11 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
     };
     Op bn[5][KS];
     T c0n[5];
-    if constexpr (!kNbrLds) load_nbr(0, bn, c0n);
+    if constexpr (kSplit) {
+      load_nbr(wu, bn, c0n);
+    } else if constexpr (!kNbrLds) {
+      load_nbr(0, bn, c0n);
+    }
     // mixed: lane group g's face (face g): the neighbour's cell mean (its load is issued here
     // and consumed after the volume integral)
     const int nbg = g == 0 ? nbr[0] : g == 1 ? nbr[1] : g == 2 ? nbr[2] : nbr[3];
@@ -256,7 +316,7 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
 
     // ------------------------------------------------------------ volume integral
 #pragma unroll 1
-    for (int qt = 0; qt < QT; ++qt) {
+    for (int qt = wu; qt < QT; qt += W) {
       Acc d[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) d[v] = Acc{0, 0, 0, 0};
@@ -323,6 +383,10 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
               const int dd = m & 3;
               b[m] = (typename Pr::E1)(dd == 3 ? T(0) : (m < 4 ? ya[dd][v] : yb[dd][v]));
             }
+            if constexpr (kSplit) {
+              split_lds<Op, QT * 10 * 64, kTag>()[((qt * 2 + jp) * 5 + v) * 64 + lane] = b;
+              continue;
+            }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
               acc[mt][v] = Pr::mfma(tab[L::proj(mt, qt, jp) * 64 + lane], b, acc[mt][v]);
@@ -331,7 +395,24 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
       }
     }
 
+    // split, mixed: fp64 cell means of the stage's state, the element's and those across lane
+    // group g's face g + 1 (face 0 for g = 3), for the mean fluxes of the epilogue
+    double sc0[5], sc0n[5];
+    const int sfg = g == 3 ? 0 : g + 1;
+    const int sng = sfg == 0 ? nbr[0] : sfg == 1 ? nbr[1] : sfg == 2 ? nbr[2] : nbr[3];
+    if constexpr (kSplit && Pr::mixed) {
+      const char* const mbase = a.mean_in ? reinterpret_cast<const char*>(a.mean_in) : ubase;
+      const uint32_t mvs = a.mean_in ? (uint32_t)(epad * sizeof(double)) : var_bytes;
+      const uint32_t mes = a.mean_in ? (uint32_t)sizeof(double) : (uint32_t)(4 * sizeof(S));
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        sc0[v] = *reinterpret_cast<const double*>(mbase + (size_t)v * mvs + (uint32_t)e * mes);
+        sc0n[v] = *reinterpret_cast<const double*>(mbase + (size_t)v * mvs + (uint32_t)(sng >= 0 ? sng : e) * mes);
+      }
+    }
+
     // ------------------------------------------------------------ face integrals
+    T fhs[9];  // split, mixed: the face's mean flux, normal and area
     if constexpr (Pr::mixed) {
       // face g of this lane's element: normal, neighbour (or ghost) mean and the mean flux,
       // staged for the whole wave (the fence orders these writes after the previous group's
@@ -344,23 +425,36 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
       if (nbg < 0) ghost_state<T>(-nbg, c0t, Ng, far, cmg);
       T fhg[5];
       num_flux<kRoe, T>(c0t, cmg, Ng, nng, gamma, fhg);
-      f2v_t* slot = lds_face + wslot * 64 + lane;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      slot[0 * 256] = f2v_t{cmg[0], cmg[1]};
-      slot[1 * 256] = f2v_t{cmg[2], cmg[3]};
-      slot[2 * 256] = f2v_t{cmg[4], fhg[0]};
-      slot[3 * 256] = f2v_t{fhg[1], fhg[2]};
-      slot[4 * 256] = f2v_t{fhg[3], fhg[4]};
-      slot[5 * 256] = f2v_t{Ng[0], Ng[1]};
-      slot[6 * 256] = f2v_t{Ng[2], nng};
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if constexpr (kSplit) {
+        // this wavefront's only face is wu: every lane takes lane group wu's record
+        auto from = [&](T x) { return __shfl(x, 16 * wu + col); };
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          c0n[v] = from(cmg[v]);
+          fhs[v] = from(fhg[v]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) fhs[5 + c] = from(Ng[c]);
+        fhs[8] = from(nng);
+      } else {
+        f2v_t* slot = lds_face + wslot * 64 + lane;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        slot[0 * 256] = f2v_t{cmg[0], cmg[1]};
+        slot[1 * 256] = f2v_t{cmg[2], cmg[3]};
+        slot[2 * 256] = f2v_t{cmg[4], fhg[0]};
+        slot[3 * 256] = f2v_t{fhg[1], fhg[2]};
+        slot[4 * 256] = f2v_t{fhg[3], fhg[4]};
+        slot[5 * 256] = f2v_t{Ng[0], Ng[1]};
+        slot[6 * 256] = f2v_t{Ng[2], nng};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
     }
 #pragma unroll 1
-    for (int f = 0; f < 4; ++f) {
+    for (int f = wu; f < 4; f += W) {
       T c0nn[5];
       T N[3];
       T nn;
@@ -379,13 +473,20 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
       }
       if constexpr (Pr::mixed) {
         // face f's record, written by lane group f of this column
-        const f2v_t* slot = lds_face + wslot * 64 + 16 * f + col;
-        const f2v_t r0 = slot[0 * 256], r1 = slot[1 * 256], r2 = slot[2 * 256], r3 = slot[3 * 256],
-                    r4 = slot[4 * 256], r5 = slot[5 * 256], r6 = slot[6 * 256];
-        c0n[0] = r0[0], c0n[1] = r0[1], c0n[2] = r1[0], c0n[3] = r1[1], c0n[4] = r2[0];
-        fhbar[0] = r2[1], fhbar[1] = r3[0], fhbar[2] = r3[1], fhbar[3] = r4[0], fhbar[4] = r4[1];
-        N[0] = r5[0], N[1] = r5[1], N[2] = r6[0];
-        nn = r6[1];
+        if constexpr (kSplit) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) fhbar[v] = fhs[v];
+          N[0] = fhs[5], N[1] = fhs[6], N[2] = fhs[7];
+          nn = fhs[8];
+        } else {
+          const f2v_t* slot = lds_face + wslot * 64 + 16 * f + col;
+          const f2v_t r0 = slot[0 * 256], r1 = slot[1 * 256], r2 = slot[2 * 256], r3 = slot[3 * 256],
+                      r4 = slot[4 * 256], r5 = slot[5 * 256], r6 = slot[6 * 256];
+          c0n[0] = r0[0], c0n[1] = r0[1], c0n[2] = r1[0], c0n[3] = r1[1], c0n[4] = r2[0];
+          fhbar[0] = r2[1], fhbar[1] = r3[0], fhbar[2] = r3[1], fhbar[3] = r4[0], fhbar[4] = r4[1];
+          N[0] = r5[0], N[1] = r5[1], N[2] = r6[0];
+          nn = r6[1];
+        }
       } else {
         face_normal<T>(f, Md, N);
         nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
@@ -427,7 +528,7 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
         }
         // the neighbour operands are consumed: request the next face's while this face's
         // own trace, fluxes and lifting are computed
-        if (!kNbrLds && f < 3 && ft == FT - 1) load_nbr(f + 1, bn, c0nn);
+        if (!kNbrLds && f + W < 4 && ft == FT - 1) load_nbr(f + W, bn, c0nn);
         // face flux (deviation) at the tile's points: fp32 values for KW = 1, packed operand
         // pairs for KW = 8 (the lift's B operand holds the four points in k = 8 g + 0..3)
         T fh[5][Pr::KW == 1 ? 4 : 1];
@@ -479,6 +580,13 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
         } else {
 #pragma unroll
           for (int v = 0; v < 5; ++v) {
+            if constexpr (kSplit) {
+              // only the first half of the operand is nonzero
+              e2_t* o = split_lds<e2_t, 4 * FT * 10 * 64, kTag>() + (((f * FT + ft) * 5 + v) * 64 + lane) * 2;
+              o[0] = fhp[v][0];
+              o[1] = fhp[v][1];
+              continue;
+            }
             Op b;
 #pragma unroll
             for (int m = 0; m < 8; ++m) b[m] = m < 4 ? fhp[v][m >> 1][m & 1] : (typename Pr::E1)0.0f;
@@ -489,6 +597,203 @@ __global__ __launch_bounds__(256, (stage_min_blocks<P, Pr>())) void stage_kernel
         }
       }
       (void)c0nn;
+    }
+
+    // ------------------------------------------------------------ split epilogue
+    if constexpr (kSplit) {
+      // (mode tile, variable) pairs 5 mt + v = wu (mod W): the state values are requested
+      // before the barrier, the pair's sum of the wavefronts' shares is taken after it
+      constexpr int NPAIR = MT * 5, NVW = (5 + W - 1) / W;
+      auto pair_v = [&](int mt, int i) { return ((wu + 5 * W - 5 * mt) & (W - 1)) + W * i; };
+      typedef S s4_t __attribute__((ext_vector_type(4)));
+      const bool live = e < mv.n_elem;
+      const bool rk = a.rk != 0;
+      auto tail_tile = [&](int mt) { return kSpread && mt == MT - 1; };
+      auto load_pair = [&](const void* base, int mt, int v, double (&x)[4]) {
+        const char* b = reinterpret_cast<const char*>(base) + (size_t)v * var_bytes;
+        if constexpr (Pr::f64) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int qd = 4 * mt + j;
+            const double y = *reinterpret_cast<const S*>(b + eoff + (uint32_t)(qd < NPQ ? qd : NPQ - 1) * quad_bytes +
+                                                         (uint32_t)g * sizeof(S));
+            x[j] = qd < NPQ ? y : 0.0;
+          }
+        } else if (tail_tile(mt)) {
+          x[0] = double(*reinterpret_cast<const S*>(b + eoff + (uint32_t)(4 * mt) * quad_bytes + (uint32_t)g * sizeof(S)));
+          x[1] = x[2] = x[3] = 0.0;
+        } else {
+          const int qd = 4 * mt + g;
+          const s4_t y = *reinterpret_cast<const s4_t*>(b + eoff + (uint32_t)(qd < NPQ ? qd : NPQ - 1) * quad_bytes);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = qd < NPQ ? double(y[j]) : 0.0;
+        }
+      };
+      double pin[MT][NVW][4], pu0[MT][NVW][4], padd[MT][NVW][4];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < NVW; ++i) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) pin[mt][i][j] = pu0[mt][i][j] = padd[mt][i][j] = 0.0;
+          const int v = pair_v(mt, i);
+          if (v < 5) {
+            if (rk) load_pair(a.u_in, mt, v, pin[mt][i]);
+            if (rk && (a.alpha != 0.0 || a.alpha_w != 0.0)) load_pair(a.u0, mt, v, pu0[mt][i]);
+            if constexpr (!Pr::mixed) {
+              if (a.r_add) load_pair(a.r_add, mt, v, padd[mt][i]);
+            }
+          }
+        }
+      const double ivol = mv.inv_vol[e];
+      // mixed: the cell-mean fluxes' B operands (as in the unsplit epilogue below)
+      double x0[5], x1[5];
+      if constexpr (Pr::mixed) {
+        const double w0 = g == 0 ? 1.0 : 0.0, w1 = g == 1 ? 1.0 : 0.0, w2 = g >= 2 ? 1.0 : 0.0;
+        double Mrow[9], y3[3][5];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          Mrow[c] = w0 * Md[c] + w1 * Md[3 + c] + w2 * Md[6 + c];
+          Mrow[3 + c] = 0.0;
+          Mrow[6 + c] = 0.0;
+        }
+        contra_flux<double>(sc0, Mrow, a.gamma - 1.0, y3);
+        double N[3], fb[5];
+        face_normal<double>(sfg, Md, N);
+        const double nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
+        if (sng < 0) ghost_state<double>(-sng, sc0, N, far64, sc0n);
+        num_flux<kRoe, double>(sc0, sc0n, N, nn, a.gamma, fb);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          x0[v] = g == 3 ? fb[v] : y3[0][v];
+          x1[v] = g == 3 ? 0.0 : fb[v];
+        }
+      }
+      // FP32 / FP64: the wavefronts' partial accumulators
+      constexpr int NR = Pr::mixed ? 1 : W * NPAIR * 64;
+      Acc* const red = Pr::mixed ? nullptr : split_lds<Acc, NR, kTag>();
+      if constexpr (!Pr::mixed) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int v = 0; v < 5; ++v) red[(wu * NPAIR + mt * 5 + v) * 64 + lane] = acc[mt][v];
+      }
+      __syncthreads();
+      using E1 = typename LiftPair<Pr>::E1;
+      typedef E1 e4_t __attribute__((ext_vector_type(4)));
+      e4_t cmp[MT][NVW];  // mixed: the pairs' companion values
+#pragma unroll
+      for (int k = 0; k < MT * NVW; ++k) {
+        const int mt = k / NVW, i = k % NVW, v = pair_v(mt, i);
+        if (v >= 5) continue;
+        Acc s = Acc{0, 0, 0, 0};
+        d4_t mean = {0, 0, 0, 0};
+        if constexpr (Pr::mixed) {
+          const Op* ops = split_lds<Op, QT * 10 * 64, kTag>();
+          typedef typename LiftPair<Pr>::type e2_t;
+          const e2_t* fops = split_lds<e2_t, 4 * FT * 10 * 64, kTag>();
+#pragma unroll
+          for (int q = 0; q < 2 * QT; ++q)
+            s = Pr::mfma(tab[L::proj(mt, q >> 1, q & 1) * 64 + lane], ops[(q * 5 + v) * 64 + lane], s);
+#pragma unroll
+          for (int ft = 0; ft < 4 * FT; ++ft) {
+            const e2_t* o = fops + ((ft * 5 + v) * 64 + lane) * 2;
+            const e2_t lo = o[0], hi = o[1];
+            Op b;
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+              b[m] = m < 2 ? lo[m & 1] : m < 4 ? hi[m & 1] : (typename Pr::E1)0.0f;
+            s = Pr::mfma(tab[L::lift(mt, ft / FT, ft % FT, 0) * 64 + lane], b, s);
+          }
+          const double xa = v == 0 ? x0[0] : v == 1 ? x0[1] : v == 2 ? x0[2] : v == 3 ? x0[3] : x0[4];
+          const double xb = v == 0 ? x1[0] : v == 1 ? x1[1] : v == 2 ? x1[2] : v == 3 ? x1[3] : x1[4];
+          mean = __builtin_amdgcn_mfma_f64_16x16x4f64(a.mean_tab[(2 * mt) * 64 + lane], xa, mean, 0, 0, 0);
+          mean = __builtin_amdgcn_mfma_f64_16x16x4f64(a.mean_tab[(2 * mt + 1) * 64 + lane], xb, mean, 0, 0, 0);
+        } else {
+          s = red[(mt * 5 + v) * 64 + lane];
+#pragma unroll
+          for (int w = 1; w < W; ++w) s += red[(w * NPAIR + mt * 5 + v) * 64 + lane];
+          if (kTail4 && mt == MT - 1) {
+            T x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              x[j] = s[j];
+              x[j] += __shfl_xor(x[j], 16);
+              x[j] += __shfl_xor(x[j], 32);
+            }
+            if constexpr (Pr::f64)
+              s = Acc{g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : x[3], 0.0, 0.0, 0.0};
+            else
+              s = Acc{x[0], x[1], x[2], x[3]};
+          }
+        }
+        const bool spread = tail_tile(mt);
+        double o[4], oc[4];  // stored values; values of the companion (the stage result)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int mode = spread ? (j == 0 ? 16 * mt + g : NP) : 16 * mt + drow_of<Pr>(g, j);
+          double r = double(s[j]) * unscale;
+          if constexpr (Pr::mixed) r += mean[j];
+          r *= ivol;
+          r += padd[mt][i][j];
+          const double out = rk ? a.alpha * pu0[mt][i][j] + (1.0 - a.alpha) * (pin[mt][i][j] + dt * r) : r;
+          const double st = a.alpha_w != 0.0 ? a.alpha_w * pu0[mt][i][j] + (1.0 - a.alpha_w) * out : out;
+          o[j] = mode < NP && live ? st : 0.0;
+          oc[j] = mode < NP && live ? out : 0.0;
+        }
+        char* const ob = reinterpret_cast<char*>(a.u_out) + (size_t)v * var_bytes + eoff;
+        if (spread) {
+          *reinterpret_cast<S*>(ob + (uint32_t)(4 * mt) * quad_bytes + (uint32_t)g * sizeof(S)) = S(o[0]);
+        } else if constexpr (!Pr::f64) {
+          const int qd = 4 * mt + g;
+          if (qd < NPQ) *reinterpret_cast<s4_t*>(ob + (uint32_t)qd * quad_bytes) = s4_t{S(o[0]), S(o[1]), S(o[2]), S(o[3])};
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (4 * mt + j < NPQ) *reinterpret_cast<S*>(ob + (uint32_t)(4 * mt + j) * quad_bytes + (uint32_t)g * sizeof(S)) = o[j];
+        }
+        if constexpr (Pr::mixed) {
+          if (a.q_out) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) cmp[mt][i][j] = to_operand<E1>(oc[j]);
+            if (mt == 0) {
+              if (g == 0) cmp[mt][i][0] = (E1)0.0f;
+              if (g == 0) {
+                a.c0_out[v * epad + e] = float(oc[0]);
+                if (a.mean_out) a.mean_out[v * epad + e] = oc[0];
+              }
+            }
+          }
+        }
+      }
+      if constexpr (Pr::mixed) {
+        if (a.q_out) {
+          // the records take the place of the projection operands, once every wavefront has
+          // read those
+          E1* const recs = reinterpret_cast<E1*>(split_lds<Op, QT * 10 * 64, kTag>());
+          __syncthreads();
+#pragma unroll
+          for (int k = 0; k < MT * NVW; ++k) {
+            const int mt = k / NVW, i = k % NVW, v = pair_v(mt, i);
+            if (v >= 5) continue;
+            E1* rec = recs + col * CES + v * (32 * KS) + 16 * mt;
+            const e4_t zero = {(E1)0.0f, (E1)0.0f, (E1)0.0f, (E1)0.0f};
+            if (tail_tile(mt)) {
+              rec[g] = cmp[mt][i][0];
+              if (g < 3) *reinterpret_cast<e4_t*>(rec + 4 * (g + 1)) = zero;
+            } else {
+              *reinterpret_cast<e4_t*>(rec + 4 * g) = cmp[mt][i];
+            }
+            if (mt == MT - 1 && 16 * MT < 32 * KS) *reinterpret_cast<e4_t*>(rec + 16 + 4 * g) = zero;
+          }
+          __syncthreads();
+          Op* q = reinterpret_cast<Op*>(a.q_out) + (size_t)grp * 16 * (5 * KS * 4);
+          const int64_t left = mv.n_elem - grp * 16;
+          for (int i = threadIdx.x; i < 16 * 5 * KS * 4; i += 64 * W)
+            if (i / (5 * KS * 4) < left) q[i] = reinterpret_cast<const Op*>(recs)[(i / (5 * KS * 4)) * (CES / 8) + i % (5 * KS * 4)];
+        }
+      }
+      return;  // one group per workgroup
     }
 
     // ------------------------------------------------------------ epilogue
@@ -897,6 +1202,17 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
       Pr::mixed ? sizeof(typename Pr::Op) / 8 * 4 * 16 * (5 * 32 * L::KS + 8) + 2 * sizeof(float) * 7 * 4 * 64 : 0;
   constexpr size_t nbr_bytes = stage_nbr_lds<P, Pr>() ? sizeof(typename Pr::Op) * 4 * 5 * L::KS * 64 : 0;
   constexpr bool lds = tab_bytes + comp_bytes + nbr_bytes <= 160 * 1024 / stage_min_blocks<P, Pr>();
+  int dev = 0, ncu = 0;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t ngroups = a.mesh.epad / 16;
+  if (a.max_blocks == 0 && 2 * ngroups <= (int64_t)ncu * split_limit<P, Pr>()) {
+    auto kern = a.flux == 1 ? stage_kernel<P, Pr, false, true, kEpiRK, kSplitWaves>
+                            : stage_kernel<P, Pr, false, false, kEpiRK, kSplitWaves>;
+    // one group per workgroup, the same number of workgroups on every XCD
+    hipLaunchKernelGGL(kern, dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(64 * kSplitWaves), 0, stream, a);
+    return hipGetLastError();
+  }
   auto kern = a.flux == 1 ? stage_kernel<P, Pr, lds, true, kEpiRK> : stage_kernel<P, Pr, lds, false, kEpiRK>;
   if constexpr (Pr::mixed || P <= 3) {  // the kernel's kFlat
     if (!a.rk)
@@ -912,15 +1228,13 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
   if (err != hipSuccess) return err;
   if (per_cu < 1) per_cu = 1;
-  int dev = 0, ncu = 0;
-  (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const int64_t ngroups = a.mesh.epad / 16;
   int64_t want = (ngroups + 3) / 4;  // one group per wavefront at least
   int64_t fill = (int64_t)ncu * per_cu;
   int64_t nblk = want < fill ? want : fill;
   if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-  if (nblk >= 8) nblk -= nblk % 8;
+  // a multiple of 8 (one share per XCD), rounded up where the chip has room, so that no wavefront
+  // takes a second group while others have none
+  if (nblk >= 8) nblk = nblk + 7 <= fill ? (nblk + 7) / 8 * 8 : nblk - nblk % 8;
   if (nblk < 1) nblk = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
   return hipGetLastError();
