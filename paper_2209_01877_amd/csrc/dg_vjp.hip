@@ -284,12 +284,37 @@ constexpr int vjp_min_blocks() {
   return (!Pr::f64 && P <= 2) ? 2 : 1;
 }
 
+template <int P, class Pr, int W>
+constexpr int vjp_wave_bound() {
+  return W > 1 ? (P <= (Pr::f64 ? 1 : 3) ? 2 : 1) : vjp_min_blocks<P, Pr>();
+}
+
+// The split kernel runs up to this many 16-element groups per two CUs.  Times in us, unsplit |
+// split, at 24, 648, 1536 and 12288 groups (256 CUs), Rusanov:
+//   FP64  P1 20.0 19.5 34.3 172 | 8.4 14.0 25.3 167      P2 46.3 48.1 82.9 429 | 15.7 40.7 78.2 614
+//         P3 96.0 122 223 1395 | 26.7 71.9 140 1147      P4 458 701 1387 8940 | 140 566 1150 9187
+//   FP32  P1 21.9 21.9 31.3 152 | 9.9 15.3 26.5 169      P2 35.1 35.6 54.1 254 | 12.8 24.2 42.8 276
+//         P3 56.3 64.4 109 531 | 20.0 45.5 82.1 566      P4 180 222 389 2194 | 61.3 193 372 2893
+// Where it is as fast at every size it is the only one: FP64 P1 and P3 (the unsplit P3 kernel
+// spilled 192 bytes per lane) and, with Roe's flux, P3 and P4 (1704 -> 1282 and 9886 -> 9094 us at
+// 12288 groups).  Otherwise the line lies below the largest mesh that the unsplit kernel takes in
+// one round of wavefronts.
+constexpr int kAlwaysSplit = 1 << 30;
+template <int P, class Pr, bool kRoe>
+constexpr int vjp_split_limit() {
+  if (Pr::f64 && (P == 3 || (P == 1 && !kRoe) || (P == 4 && kRoe))) return kAlwaysSplit;
+  return (Pr::f64 && P == 2) || (!Pr::f64 && P == 4) ? 5 : 12;
+}
+
 // kRoe selects the face flux at compile time (Roe's adjoint needs more registers).  FP32 up
 // to P2 fits two waves per SIMD; FP64 and higher orders take one.  kLds: the operand tables
 // are copied into LDS once per workgroup (every MFMA A operand is then an LDS read instead
 // of an L1/L2 access); P4 FP64 (320 KB) and P4 FP32 (160 KB) read them from global memory.
-template <int P, class Pr, bool kRoe, bool kLds>
-__global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(VjpArgs a) {
+// W: wavefronts that share one 16-element group: 1, or 4 on small meshes (vjp_split_limit), as
+// in the stage kernel: wavefront w takes face w and the volume point tiles w, w + 4, ..., the
+// partial sums meet in LDS and the epilogue's (mode tile, variable) pairs are dealt out.
+template <int P, class Pr, bool kRoe, bool kLds, int W = 1>
+__global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(VjpArgs a) {
   using O = Ord<P>;
   using V = VjpLayout<P>;
   using S = typename Pr::S;
@@ -298,6 +323,11 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
   using Acc = typename Pr::Acc;
   constexpr int NP = O::NP, NQ = O::NQ, NF = O::NF, MT = O::MT, QT = O::QT, FT = O::FT, KS = V::KS;
   static_assert(Pr::KW == 1, "the adjoint uses the f64/f32 instructions");
+  constexpr bool kSplit = W > 1;
+  // split: the element's own operands and, across the face, the volume part wait in LDS where that
+  // makes two waves per SIMD fit (FP32 P4: one wave, the own operands alone); the FP64 kernels of
+  // P2 and up would spill either way
+  constexpr bool kOwnLds = kSplit && (!Pr::f64 || P == 1);
 
   __shared__ Op lds_tab[kLds ? V::n_slots * 64 : 1];
   const Op* __restrict__ vt;
@@ -336,12 +366,19 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
   const int nwb = blockDim.x >> 6;
   const int nx = (nblk % 8 == 0) ? 8 : 1;
   const int xcd = blockIdx.x % nx;
-  const int64_t waves_x = (int64_t)(nblk / nx) * nwb;
-  const int64_t wave_x = (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);
+  const int64_t waves_x = (int64_t)(nblk / nx) * (kSplit ? 1 : nwb);
+  const int64_t wave_x = kSplit ? blockIdx.x / nx : (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);
   const int64_t ngroups = epad / 16;
   const int64_t chunk = (ngroups + nx - 1) / nx;
   const int64_t g_begin = xcd * chunk;
   const int64_t g_end = g_begin + chunk < ngroups ? g_begin + chunk : ngroups;
+
+  // a split wavefront's number: its face and first volume point tile
+  const int wu = kSplit ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  constexpr bool kVolLds = kSplit && vjp_wave_bound<P, Pr, W>() == 2;
+  constexpr int RS = MT * 5 * 64;  // a wavefront's share of lds_red
+  __shared__ Acc lds_red[kSplit ? W * RS : 1];
+  __shared__ Op lds_own[kOwnLds ? 10 * KS * 64 : 1];
 
   for (int64_t grp = g_begin + wave_x; grp < g_end; grp += waves_x) {
     const int e = (int)(grp * 16 + col);
@@ -359,9 +396,27 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
 #pragma unroll
     for (int f = 0; f < 4; ++f) nbr[f] = mv.nbr[f * epad + e];
 
+    // the element's own operands: in registers, or (split) in LDS, where the wavefronts share
+    // them: wavefront w brings every fourth of the ten variables
     Op bc[5][KS], bw[5][KS];
-    load_ops<Pr, NP, KS>(ubase, var_bytes, eoff, off, keep, T(1), bc);
-    load_ops<Pr, NP, KS>(wbase, var_bytes, eoff, off, keep, ivol, bw);
+    if constexpr (kOwnLds) {
+      for (int i = wu; i < 10; i += W) {
+        const int v = i < 5 ? i : i - 5;
+        const char* base = (i < 5 ? ubase : wbase) + (size_t)v * var_bytes + eoff;
+        const T scale = i < 5 ? T(1) : ivol;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          const S x = *reinterpret_cast<const S*>(base + off[s]);
+          lds_own[(i * KS + s) * 64 + lane] = keep[s] ? Op(scale * x) : Op(0);
+        }
+      }
+      __syncthreads();
+    } else {
+      load_ops<Pr, NP, KS>(ubase, var_bytes, eoff, off, keep, T(1), bc);
+      load_ops<Pr, NP, KS>(wbase, var_bytes, eoff, off, keep, ivol, bw);
+    }
+    auto own_u = [&](int v, int s) { return kOwnLds ? lds_own[(v * KS + s) * 64 + lane] : bc[v][s]; };
+    auto own_w = [&](int v, int s) { return kOwnLds ? lds_own[((5 + v) * KS + s) * 64 + lane] : bw[v][s]; };
 
     Acc acc[MT][5];
 #pragma unroll
@@ -371,7 +426,7 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
 
     // ------------------------------------------------------------ volume
 #pragma unroll 1
-    for (int qt = 0; qt < QT; ++qt) {
+    for (int qt = wu; qt < QT; qt += W) {
       Acc du[5], dg[3][5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
@@ -383,12 +438,12 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
       for (int s = 0; s < KS; ++s) {
         const Op av = vt[V::interp(qt, s) * 64 + lane];
 #pragma unroll
-        for (int v = 0; v < 5; ++v) du[v] = Pr::mfma(av, bc[v][s], du[v]);
+        for (int v = 0; v < 5; ++v) du[v] = Pr::mfma(av, own_u(v, s), du[v]);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           const Op ad = vt[V::tinterp(qt, d, s) * 64 + lane];
 #pragma unroll
-          for (int v = 0; v < 5; ++v) dg[d][v] = Pr::mfma(ad, bw[v][s], dg[d][v]);
+          for (int v = 0; v < 5; ++v) dg[d][v] = Pr::mfma(ad, own_w(v, s), dg[d][v]);
         }
       }
 #pragma unroll
@@ -418,9 +473,20 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
       }
     }
 
+    if constexpr (kVolLds) {
+      // the volume part waits in LDS: its registers are free for the face
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          lds_red[wu * RS + (mt * 5 + v) * 64 + lane] = acc[mt][v];
+          acc[mt][v] = Acc{0, 0, 0, 0};
+        }
+    }
+
     // ------------------------------------------------------------ faces
 #pragma unroll 1
-    for (int f = 0; f < 4; ++f) {
+    for (int f = wu; f < 4; f += W) {
       T N[3];
       face_normal<T>(f, Md, N);
       const T nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
@@ -443,8 +509,8 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
           const Op aw = vt[V::ttrace(f, ft, s) * 64 + lane];
 #pragma unroll
           for (int v = 0; v < 5; ++v) {
-            dm[v] = Pr::mfma(av, bc[v][s], dm[v]);
-            wm[v] = Pr::mfma(aw, bw[v][s], wm[v]);
+            dm[v] = Pr::mfma(av, own_u(v, s), dm[v]);
+            wm[v] = Pr::mfma(aw, own_w(v, s), wm[v]);
           }
         }
 #pragma unroll 1
@@ -510,6 +576,41 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
       }
     }
 
+
+    if constexpr (kSplit) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          Acc& r = lds_red[wu * RS + (mt * 5 + v) * 64 + lane];
+          r = kVolLds ? r + acc[mt][v] : acc[mt][v];
+        }
+      __syncthreads();
+      if (e >= mv.n_elem) return;
+#pragma unroll 1
+      for (int pr = wu; pr < 5 * MT; pr += W) {
+        const int mt = pr / 5, v = pr % 5;
+        Acc t = lds_red[pr * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) t += lds_red[w * RS + pr * 64 + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int mode = 16 * mt + drow_of<Pr>(g, j);
+          if ((mode >> 2) < NPQ) {
+            const size_t o = (size_t)v * var_bytes + moff(mode) + eoff;
+            double r = 0.0;
+            if (mode < NP) {
+              r = a.c * double(t[j]);
+              for (int k = 0; k < a.n_terms; ++k)
+                r += a.ya[k] * double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(a.y[k]) + o));
+            }
+            *reinterpret_cast<S*>(obase + o) = S(r);
+          }
+        }
+      }
+      return;  // one group per workgroup
+    }
+
     if (e < mv.n_elem) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
@@ -535,28 +636,43 @@ __global__ __launch_bounds__(256, (vjp_min_blocks<P, Pr>())) void vjp_kernel(Vjp
   }
 }
 
-template <int P, class Pr>
-hipError_t launch_vjp_impl(const VjpArgs& a, hipStream_t stream) {
-  // tables in LDS when they fit in the share of one workgroup (160 KB per CU over the
-  // workgroups resident per CU)
-  constexpr bool lds = sizeof(typename Pr::Op) * VjpLayout<P>::n_slots * 64 <= 160 * 1024 / vjp_min_blocks<P, Pr>();
-  auto kern = a.flux == 1 ? vjp_kernel<P, Pr, true, lds> : vjp_kernel<P, Pr, false, lds>;
-  int per_cu = 0;
-  hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
-  if (err != hipSuccess) return err;
-  if (per_cu < 1) per_cu = 1;
+template <int P, class Pr, bool kRoe>
+hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
   int dev = 0, ncu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t ngroups = a.mesh.epad / 16;
-  int64_t want = (ngroups + 3) / 4;
-  int64_t fill = (int64_t)ncu * per_cu;
-  int64_t nblk = want < fill ? want : fill;
-  if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-  if (nblk >= 8) nblk -= nblk % 8;
-  if (nblk < 1) nblk = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
+  constexpr int limit = vjp_split_limit<P, Pr, kRoe>();
+  if (limit == kAlwaysSplit || (a.max_blocks == 0 && 2 * ngroups <= (int64_t)ncu * limit)) {
+    // one group per workgroup, the same number of workgroups on every XCD
+    hipLaunchKernelGGL((vjp_kernel<P, Pr, kRoe, false, 4>), dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(256), 0,
+                       stream, a);
+    return hipGetLastError();
+  }
+  if constexpr (limit != kAlwaysSplit) {
+    // tables in LDS when they fit in the share of one workgroup (160 KB per CU over the
+    // workgroups resident per CU)
+    constexpr bool lds = sizeof(typename Pr::Op) * VjpLayout<P>::n_slots * 64 <= 160 * 1024 / vjp_min_blocks<P, Pr>();
+    auto kern = vjp_kernel<P, Pr, kRoe, lds>;
+    int per_cu = 0;
+    hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
+    if (err != hipSuccess) return err;
+    if (per_cu < 1) per_cu = 1;
+    int64_t want = (ngroups + 3) / 4;
+    int64_t fill = (int64_t)ncu * per_cu;
+    int64_t nblk = want < fill ? want : fill;
+    if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
+    // a multiple of 8 (one share per XCD), rounded up where the chip has room
+    if (nblk >= 8) nblk = nblk + 7 <= fill ? (nblk + 7) / 8 * 8 : nblk - nblk % 8;
+    if (nblk < 1) nblk = 1;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
+  }
   return hipGetLastError();
+}
+
+template <int P, class Pr>
+hipError_t launch_vjp_impl(const VjpArgs& a, hipStream_t stream) {
+  return a.flux == 1 ? launch_vjp_flux<P, Pr, true>(a, stream) : launch_vjp_flux<P, Pr, false>(a, stream);
 }
 
 }  // namespace

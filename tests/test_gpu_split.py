@@ -49,3 +49,30 @@ def test_stage_both_sides_of_the_line(p, size, prec):
     assert_parity(dg, out[sample], ref, TOL[prec], vol=vol, l2_scale=l2, elem_scale=(0.25 * R).abs().amax((0, 2)),
                   label=f"{size} p={p} {prec} stage")
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("flux", ["rusanov", "roe"])
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_vjp_of_disjoint_copies(p, prec, flux):
+    """The adjoint of eight disjoint copies of a mesh (above the line) is eight times that of one
+    (below it, the form the oracle tests run), to the rounding of another summation order."""
+    mesh, _, U, W, _, _ = walls("below", p, "roe" if p % 2 else "rusanov")
+    n_vert = int(mesh.elem_vid.max()) + 1
+
+    def vjp(copies):
+        shift = np.arange(copies)[:, None, None] * n_vert
+        many = kuhn_cube(1, periodic=(False, False, True))
+        many.elem_vid = (mesh.elem_vid[None] + shift).reshape(-1, 4)
+        many.elem_xyz = np.tile(mesh.elem_xyz, (copies, 1, 1))
+        many.bface_vid = (mesh.bface_vid[None] + shift).reshape(-1, 3)
+        many.bface_tag = np.tile(mesh.bface_tag, copies)
+        s = solver(p, prec, many, farfield=FAR)
+        s.set_flux(flux)
+        Ui, Wi, Yi = (s.set_state(X.repeat(copies, 1, 1).cuda()) for X in (U, W, U + W))
+        return s.get_state(s.residual_vjp_axpy(Ui, Wi, 0.3, [(0.7, Yi)], s.new_state())).cpu().view(copies, *U.shape)
+
+    one, eight = vjp(1), vjp(8)
+    err = ((eight - one).norm() / (math.sqrt(8) * one.norm())).item()
+    print(f"{prec} p={p} {flux}: copies differ by {err:.1e}")
+    assert err < {"fp64": 1e-13, "fp32": 1e-5}[prec]
