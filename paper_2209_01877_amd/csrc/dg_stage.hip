@@ -186,12 +186,9 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
   const int64_t epad = mv.epad;
   constexpr int NPQ = npq_of(NP);
   // FP32 / FP64: when the last mode tile holds at most 4 modes (P1, P3, P4), a 16-row MFMA
-  // would waste 12 of its rows.  Its projection and lift instead let lane group g
-  // accumulate its own points' share of those modes for its 16 elements — as 4x4x1 MFMA
-  // blocks in fp32 (a quarter of the 16x16x4 cost), as fp64 FMAs with the four table
-  // values read once per lane group — and the four shares are summed across lane groups
-  // before the epilogue.
+  // would waste 12 of its rows: its projection and lift take the blocked 4x4 forms (mfma_tile).
   constexpr bool kTail4 = Pr::KW == 1 && NP - 16 * (MT - 1) <= 4;
+  constexpr bool kTailFma = kTail4 && Pr::f64 && P == 4 && !kSplit;
   // Mixed modes, P3 and P4: the last mode tile holds at most 4 modes.  Its table rows put
   // mode 16 (MT - 1) + g in register 0 of lane group g (fp32 accumulator row 4 g, fp64
   // accumulator row g) and zeros elsewhere, so that the epilogue handles that tile as one
@@ -358,7 +355,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int dd = 0; dd < 3; ++dd) {
-              if constexpr (kTail4 && Pr::f64) {
+              if constexpr (kTailFma) {
                 if (mt == MT - 1) {
                   tail_fma<Pr>(tab + L::proj(mt, qt, 4 * dd + j) * 64 + 16 * g, yy[dd], acc[mt]);
                   continue;
@@ -564,7 +561,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int lk = 0; lk < 4; ++lk) {
-              if constexpr (kTail4 && Pr::f64) {
+              if constexpr (kTailFma) {
                 if (mt == MT - 1) {
                   T fl[5];
 #pragma unroll
@@ -713,18 +710,14 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           s = red[(mt * 5 + v) * 64 + lane];
 #pragma unroll
           for (int w = 1; w < W; ++w) s += red[(w * NPAIR + mt * 5 + v) * 64 + lane];
-          if (kTail4 && mt == MT - 1) {
-            T x[4];
+          if (kTail4 && !Pr::f64 && mt == MT - 1) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              x[j] = s[j];
-              x[j] += __shfl_xor(x[j], 16);
-              x[j] += __shfl_xor(x[j], 32);
+              T x = s[j];
+              x += __shfl_xor(x, 16);
+              x += __shfl_xor(x, 32);
+              s[j] = x;
             }
-            if constexpr (Pr::f64)
-              s = Acc{g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : x[3], 0.0, 0.0, 0.0};
-            else
-              s = Acc{x[0], x[1], x[2], x[3]};
           }
         }
         const bool spread = tail_tile(mt);
@@ -802,7 +795,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
     // tile.  Lane group g supplies k = g (volume direction g, or face 0 for g = 3) and
     // k = 4 + g (face g + 1, or zero); the table rows are permuted so that the fp64
     // accumulator rows line up with the fp32 accumulator rows of the same lane.
-    if constexpr (kTail4) {
+    if constexpr (kTail4 && (!Pr::f64 || kTailFma)) {
       // sum the lane groups' shares of the last tile (register r: mode 16 (MT - 1) + r) and
       // move them to the accumulator rows of the precision: fp32 row 4 g + j (lane group 0
       // holds the tile's modes in its registers), fp64 row g + 4 j (mode r in register 0

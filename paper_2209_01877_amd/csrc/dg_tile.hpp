@@ -55,20 +55,36 @@ __device__ __forceinline__ void load_operands(const char* __restrict__ base, uin
   }
 }
 
-// Projection / lift MFMA for one mode tile: the 4x4x1 block form for the short last
-// tile of the fp32 path (see kTail4; fp64 handles that tile with tail_fma), else the
-// precision's 16x16 instruction.
+// Projection / lift MFMA for one mode tile: the precision's 16x16 instruction, or for a short last
+// tile of at most 4 modes (kTail4) one of the blocked 4x4 forms, whose B operand is the same.
+// FP64, 4x4x4 in four blocks: block b holds columns 4 b .. 4 b + 3, the four rows are the tile's
+// modes and k runs over the lane groups' points, so accumulator register 0 of lane group r holds
+// mode r (what the 16x16 form would put there).  It takes 20 cycles and one accumulator where
+// four FMAs per variable on the lane group's own point took 32 cycles, four accumulators and a
+// sum over the lane groups: FP64 stage, 48^3 x 6 elements, P1 291 -> 241 us, P3 1665 -> 1602 us.
+// FP32, 4x4x1 in sixteen blocks: each lane group accumulates its own points'
+// share of the modes in registers 0..3, summed over the lane groups at the end.
 template <class Pr, bool kTail4>
 __device__ __forceinline__ typename Pr::Acc mfma_tile(bool last, typename Pr::Op a, typename Pr::Op b,
                                                       typename Pr::Acc c) {
-  if constexpr (kTail4 && !Pr::f64) {
-    if (last) return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+  if constexpr (kTail4) {
+    if (last) {
+      if constexpr (Pr::f64) {
+        c[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c[0], 0, 0, 0);
+        return c;
+      } else {
+        return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+      }
+    }
   }
   return Pr::mfma(a, b, c);
 }
 
-// FP64 short last tile: acc[v][r] += A[r] y[v] for the tile's modes r = 0..3, with the
-// four table values of this lane group's point read once (a broadcast within the group).
+// FP64 short last tile as FMAs: acc[v][r] += A[r] y[v] for the tile's modes r = 0..3, with the
+// four table values of this lane group's point read once (a broadcast within the group).  Kept
+// for the unsplit P4 stage kernel, which reads its tables from global memory at one wave per
+// SIMD: there the MFMA form, whose operand is a whole table slot, took 2716 against 2113 us
+// (32^3 x 6 elements).
 template <class Pr>
 __device__ __forceinline__ void tail_fma(const typename Pr::Op* __restrict__ t, const typename Pr::T (&y)[5],
                                          typename Pr::Acc (&acc)[5]) {
