@@ -37,9 +37,9 @@ struct tdg_ctx {
          off_mom = 0, off_mtab = 0, off_qx = 0, off_qw = 0, off_B = 0, off_fw = 0, off_Bf = 0, off_comp = 0, total = 0;
   double far[5] = {1.0, 0.0, 0.0, 0.0, 2.5};
   int flux = TDG_FLUX_RUSANOV;
-  // viscous (Navier-Stokes, BR1) terms: off when mu == 0; scratch Z (3 states) and Rv
+  // viscous (Navier-Stokes, BR1) terms: off when mu == 0; scratch: a residual and the own-half face fluxes
   double mu = 0.0, prandtl = 0.72;
-  size_t off_z = 0, off_rv = 0, off_hb = 0;
+  size_t off_rv = 0, off_hb = 0;
 };
 
 namespace {
@@ -486,10 +486,9 @@ int tdg_mesh_upload(tdg_ctx* c, int64_t n_elem, const int64_t* elem_vid, const d
     c->off_Bf = take(c->ref.Bf.size() * sizeof(double));
     // mixed modes: scratch operand companion for single residual / stage calls
     c->off_comp = take(c->prec >= TDG_MIXED_BF16 ? companion_bytes(c->p, epad) : 0);
-    // viscous scratch: Z = grad U (15 state-layout variables) and the viscous residual part
+    // viscous scratch: the residual without the neighbours' viscous halves
     {
       const size_t sb = (size_t)5 * ((c->ref.np + 3) / 4) * epad * 4 * (c->prec == TDG_FP32 ? 4 : 8);
-      c->off_z = take(c->mu > 0.0 ? 3 * sb : 0);
       c->off_rv = take(c->mu > 0.0 ? sb : 0);
       // own-half viscous face fluxes at the face points (padded to whole 16-point tiles),
       // 4 faces x 5 variables per element
@@ -676,31 +675,33 @@ int tdg_work_bytes(const tdg_ctx* c, size_t* bytes) {
   return TDG_OK;
 }
 
-// Viscous terms of U (mu > 0): Z = grad U, then the viscous residual part into the
-// context's scratch, which the next stage launch adds to R through a.r_add.
-static hipError_t viscous_part(tdg_ctx* c, const void* U, StageArgs& a, hipStream_t s) {
-  a.r_add = nullptr;
-  if (!(c->mu > 0.0)) return hipSuccess;
+// The residual (a.rk == 0) or stage update described by `a`: the stage kernel, or with viscous
+// terms (mu > 0) the two viscous kernels, whose intermediate residual and face fluxes live in the
+// context's scratch.
+static hipError_t launch_rhs(tdg_ctx* c, const StageArgs& a, hipStream_t s) {
+  if (!(c->mu > 0.0)) return launch_stage(c->p, c->prec, a, s);
   ViscArgs v;
   std::memset(&v, 0, sizeof(v));
-  v.u = U;
-  v.z = c->dev + c->off_z;
-  v.out = c->dev + c->off_z;
-  v.mesh = view(c);
-  v.tab = c->dev + c->off_stab;
+  v.u = a.u_in;
+  v.out = c->dev + c->off_rv;
+  v.flux = a.flux;
+  v.mesh = a.mesh;
+  v.tab = a.tab;
   v.gamma = c->gamma;
   v.mu = c->mu;
   v.prandtl = c->prandtl;
   for (int k = 0; k < 5; ++k) v.far[k] = c->far[k];
   v.hbuf = c->dev + c->off_hb;
-  hipError_t e = launch_grad(c->p, c->prec, v, s);
+  hipError_t e = launch_ns(c->p, c->prec, v, s);
   if (e != hipSuccess) return e;
-  v.out = c->dev + c->off_rv;
-  e = launch_visc(c->p, c->prec, v, s);
-  if (e != hipSuccess) return e;
-  e = launch_visc_nbr(c->p, c->prec, v, s);
-  a.r_add = c->dev + c->off_rv;
-  return e;
+  v.r_own = v.out;
+  v.u0 = a.u0;
+  v.out = a.u_out;
+  v.alpha = a.alpha;
+  v.dt = a.dt;
+  v.dt_dev = a.dt_dev;
+  v.rk = a.rk;
+  return launch_ns_update(c->p, c->prec, v, s);
 }
 
 int tdg_residual(tdg_ctx* c, const void* U, void* R, void* s) {
@@ -712,13 +713,11 @@ int tdg_residual(tdg_ctx* c, const void* U, void* R, void* s) {
     hipError_t e = pack_scratch(c, U, a, (hipStream_t)s);
     if (e != hipSuccess) return hip_fail(c, e, "pack launch");
   }
-  hipError_t ev = viscous_part(c, U, a, (hipStream_t)s);
-  if (ev != hipSuccess) return hip_fail(c, ev, "viscous launch");
   a.u_in = U;
   a.u0 = U;
   a.u_out = R;
   a.rk = 0;
-  hipError_t e = launch_stage(c->p, c->prec, a, (hipStream_t)s);
+  hipError_t e = launch_rhs(c, a, (hipStream_t)s);
   return e == hipSuccess ? TDG_OK : hip_fail(c, e, "residual launch");
 }
 
@@ -771,9 +770,7 @@ int tdg_rk_step(tdg_ctx* c, void* U, void* work, double dt, int n_steps, void* s
         a.alpha = 0.0;
         a.u0 = nullptr;
       }
-      hipError_t e = viscous_part(c, a.u_in, a, (hipStream_t)s);
-      if (e != hipSuccess) return hip_fail(c, e, "viscous launch");
-      e = launch_stage(c->p, c->prec, a, (hipStream_t)s);
+      hipError_t e = launch_rhs(c, a, (hipStream_t)s);
       if (e != hipSuccess) return hip_fail(c, e, "rk stage launch");
     }
   }
@@ -832,9 +829,7 @@ int tdg_rk_step_adaptive(tdg_ctx* c, void* U, void* work, double cfl, int n_step
         a.alpha = 0.0;
         a.u0 = nullptr;
       }
-      e = viscous_part(c, a.u_in, a, (hipStream_t)s);
-      if (e != hipSuccess) return hip_fail(c, e, "viscous launch");
-      e = launch_stage(c->p, c->prec, a, (hipStream_t)s);
+      e = launch_rhs(c, a, (hipStream_t)s);
       if (e != hipSuccess) return hip_fail(c, e, "rk stage launch");
     }
   }
@@ -858,9 +853,7 @@ int tdg_rk_stage(tdg_ctx* c, const void* U_in, const void* U0, void* U_out, doub
   a.u_in = U_in;
   a.u0 = U0;
   a.u_out = U_out;
-  hipError_t ev = viscous_part(c, U_in, a, (hipStream_t)s);
-  if (ev != hipSuccess) return hip_fail(c, ev, "viscous launch");
-  hipError_t e = launch_stage(c->p, c->prec, a, (hipStream_t)s);
+  hipError_t e = launch_rhs(c, a, (hipStream_t)s);
   return e == hipSuccess ? TDG_OK : hip_fail(c, e, "rk stage launch");
 }
 

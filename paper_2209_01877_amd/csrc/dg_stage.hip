@@ -626,20 +626,17 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           for (int j = 0; j < 4; ++j) x[j] = qd < NPQ ? double(y[j]) : 0.0;
         }
       };
-      double pin[MT][NVW][4], pu0[MT][NVW][4], padd[MT][NVW][4];
+      double pin[MT][NVW][4], pu0[MT][NVW][4];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int i = 0; i < NVW; ++i) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) pin[mt][i][j] = pu0[mt][i][j] = padd[mt][i][j] = 0.0;
+          for (int j = 0; j < 4; ++j) pin[mt][i][j] = pu0[mt][i][j] = 0.0;
           const int v = pair_v(mt, i);
           if (v < 5) {
             if (rk) load_pair(a.u_in, mt, v, pin[mt][i]);
             if (rk && (a.alpha != 0.0 || a.alpha_w != 0.0)) load_pair(a.u0, mt, v, pu0[mt][i]);
-            if constexpr (!Pr::mixed) {
-              if (a.r_add) load_pair(a.r_add, mt, v, padd[mt][i]);
-            }
           }
         }
       const double ivol = mv.inv_vol[e];
@@ -728,7 +725,6 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           double r = double(s[j]) * unscale;
           if constexpr (Pr::mixed) r += mean[j];
           r *= ivol;
-          r += padd[mt][i][j];
           const double out = rk ? a.alpha * pu0[mt][i][j] + (1.0 - a.alpha) * (pin[mt][i][j] + dt * r) : r;
           const double st = a.alpha_w != 0.0 ? a.alpha_w * pu0[mt][i][j] + (1.0 - a.alpha_w) * out : out;
           o[j] = mode < NP && live ? st : 0.0;
@@ -854,7 +850,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
     // State values of mode tile mt (mode = 16 mt + drow(g, j)): with the fp32 accumulator
     // layout they form one mode quad per lane (one vector access); with the fp64 layout
     // they sit at position g of four quads.  Padding modes of the last quad are written 0.
-    double uin[5][4], u0v[5][4], radd[5][4];
+    double uin[5][4], u0v[5][4];
     // kSpread: the last tile's values, one per lane (mode 16 (MT - 1) + g at position g of
     // quad 4 (MT - 1)), requested together with those of the tile before it
     double tin[kSpread ? 5 : 1], t0v[kSpread ? 5 : 1];
@@ -890,23 +886,8 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
 #pragma unroll
       for (int v = 0; v < 5; ++v)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) uin[v][j] = u0v[v][j] = radd[v][j] = 0.0;
+        for (int j = 0; j < 4; ++j) uin[v][j] = u0v[v][j] = 0.0;
       if (!kFlat && !live) return;
-      if constexpr (!Pr::mixed) {
-        // an added residual part (the viscous terms) in the state's layout and precision
-        if (a.r_add) {
-          const char* rb = reinterpret_cast<const char*>(a.r_add);
-#pragma unroll
-          for (int v = 0; v < 5; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int mode = 16 * mt + drow_of<Pr>(g, j);
-              if ((mode >> 2) < NPQ)
-                radd[v][j] = double(*reinterpret_cast<const S*>(rb + (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
-                                                                 ((size_t)e * 4 + (mode & 3)) * sizeof(S)));
-            }
-        }
-      }
       if (!rk) return;
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
@@ -1022,7 +1003,6 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
           double r = double(acc[mt][v][j]) * unscale;
           if constexpr (Pr::mixed) r += mean[j];
           r *= ivol;
-          r += radd[v][j];
           const double ui = spread ? tin[kSpread ? v : 0] : uin[v][j];
           const double u0 = spread ? t0v[kSpread ? v : 0] : u0v[v][j];
           const double out = rk ? a.alpha * u0 + (1.0 - a.alpha) * (ui + dt * r) : r;

@@ -7,18 +7,17 @@
 //   |K| Z_k,i = -sum_q w_q |det J| dphi_i/dx_k U(q) + sum_f sum_q w^f_q (U- + U+)/2 N_k phi_i
 //   Rv_i      = -(Vv_i - Sv_i) / |K|,   Vv_i = int_K F_v(U, Z) . grad phi_i,
 //               Sv_i = sum_f int_f (F_v(U-, Z-) + F_v(U+, Z+))/2 . n phi_i
-// with the inviscid ghost state as U+ on boundary faces and Z+ = Z- there.  Three kernels,
-// each in the column-tile structure of the stage kernel (16 elements per wavefront, the
-// same MFMA operand tables):
-//   grad_kernel     : Z for the three directions (stored as 15 state-layout variables 5 k + v)
-//   visc_kernel     : the volume term and the element's own half of every face term of Rv;
-//                     the own half F_v(U-, Z-) . N / 2 at the face points is also stored
-//   visc_nbr_kernel : adds the neighbours' halves, read from that store, to Rv
-// Rv is read by the stage kernel's epilogue as an added residual.  Since the BR1 interface
-// flux is an average, the face term splits into two halves; the neighbour's half at our
-// face points is minus its own half at its face points (opposite normal, and two elements
-// sharing a face parametrise it identically), so it is computed once, by its owner.  Each
-// kernel writes only its own elements' outputs: no atomics.
+// with the inviscid ghost state as U+ on boundary faces and Z+ = Z- there.  Two kernels, with the
+// stage kernel's MFMA operand tables:
+//   ns_kernel        : everything of the residual that an element's own Z gives: the lifting of Z,
+//                      the inviscid and viscous volume terms, the inviscid face fluxes and the
+//                      element's own half of every viscous face term; the own half
+//                      F_v(U-, Z-) . N / 2 at the face points is also stored
+//   ns_update_kernel : adds the neighbours' halves, read from that store, then the RK update
+// Since the BR1 interface flux is an average, the face term splits into two halves; the
+// neighbour's half at our face points is minus its own half at its face points (opposite normal,
+// and two elements sharing a face parametrise it identically), so it is computed once, by its
+// owner.  Each kernel writes only its own elements' outputs: no atomics.
 #include <hip/hip_runtime.h>
 
 #include "dg_kernels.hpp"
@@ -66,95 +65,12 @@ __device__ __forceinline__ void visc_flux(const T U[5], const T Z[3][5], T gm1, 
   }
 }
 
-// FP32 up to P3 fits two waves per SIMD without spilling; FP64 and P4 take one.
-template <int P, class Pr>
-constexpr int visc_min_blocks() {
-  return (!Pr::f64 && P <= 3) ? 2 : 1;
-}
-
-template <int P, class Pr>
-constexpr bool visc_lds() {
-  // at most 96 KB, and within the LDS share of each resident workgroup (160 KB per CU)
-  constexpr size_t share = 160 * 1024 / visc_min_blocks<P, Pr>();
-  return sizeof(typename Pr::Op) * Layout<P, 1>::n_slots * 64 <= (share < 96 * 1024 ? share : 96 * 1024);
-}
-
-// Shared prologue: tables (LDS when they fit), lane coordinates, the XCD-local sweep.
-#define TDG_VISC_PROLOGUE                                                                          \
-  using O = Ord<P>;                                                                                \
-  using L = Layout<P, 1>;                                                                          \
-  using S = typename Pr::S;                                                                        \
-  using T = typename Pr::T;                                                                        \
-  using Op = typename Pr::Op;                                                                      \
-  using Acc = typename Pr::Acc;                                                                    \
-  constexpr int NP = O::NP, NQ = O::NQ, NF = O::NF, MT = O::MT, QT = O::QT, FT = O::FT, KS = L::KS; \
-  constexpr int NPQ = npq_of(NP);                                                                  \
-  constexpr bool kTail4 = NP - 16 * (MT - 1) <= 4;                                                 \
-  constexpr bool kLds = visc_lds<P, Pr>();                                                         \
-  __shared__ Op lds_tab[kLds ? L::n_slots * 64 : 1];                                               \
-  const Op* __restrict__ tab;                                                                      \
-  if constexpr (kLds) {                                                                            \
-    const Op* src = reinterpret_cast<const Op*>(a.tab);                                            \
-    for (int i = threadIdx.x; i < L::n_slots * 64; i += blockDim.x) lds_tab[i] = src[i];           \
-    __syncthreads();                                                                               \
-    tab = lds_tab;                                                                                 \
-  } else {                                                                                         \
-    tab = reinterpret_cast<const Op*>(a.tab);                                                      \
-  }                                                                                                \
-  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;                               \
-  const MeshView& mv = a.mesh;                                                                     \
-  const int64_t epad = mv.epad;                                                                    \
-  const uint32_t quad_bytes = (uint32_t)(epad * 4 * sizeof(S));                                    \
-  const uint32_t var_bytes = quad_bytes * NPQ;                                                     \
-  const char* __restrict__ ubase = reinterpret_cast<const char*>(a.u);                             \
-  const T gamma = T(a.gamma), gm1 = T(a.gamma - 1.0);                                              \
-  T far[5];                                                                                        \
-  for (int v = 0; v < 5; ++v) far[v] = T(a.far[v]);                                                \
-  OperandMap<Pr, NP, KS> om;                                                                       \
-  om.init(g, quad_bytes);                                                                          \
-  const int nblk = gridDim.x;                                                                      \
-  const int nwb = blockDim.x >> 6;                                                                 \
-  const int nx = (nblk % 8 == 0) ? 8 : 1;                                                          \
-  const int xcd = blockIdx.x % nx;                                                                 \
-  const int64_t waves_x = (int64_t)(nblk / nx) * nwb;                                              \
-  const int64_t wave_x = (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);                    \
-  const int64_t ngroups = epad / 16;                                                               \
-  const int64_t chunk = (ngroups + nx - 1) / nx;                                                   \
-  const int64_t g_begin = xcd * chunk;                                                             \
-  const int64_t g_end = g_begin + chunk < ngroups ? g_begin + chunk : ngroups;
-
-// Accumulate the projection of one 16-point tile: acc[mt][v] += P(mt, qt, 4 dd + j) y[dd][v].
-template <class Pr, int MT, bool kTail4, class L>
-__device__ __forceinline__ void project_point(const typename Pr::Op* __restrict__ tab, int qt, int j, int lane, int g,
-                                              typename Pr::T (&y)[3][5], typename Pr::Acc (&acc)[MT][5]) {
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int dd = 0; dd < 3; ++dd) {
-      if constexpr (kTail4 && Pr::f64) {
-        if (mt == MT - 1) {
-          tail_fma<Pr>(tab + L::proj(mt, qt, 4 * dd + j) * 64 + 16 * g, y[dd], acc[mt]);
-          continue;
-        }
-      }
-      const typename Pr::Op av = tab[L::proj(mt, qt, 4 * dd + j) * 64 + lane];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) acc[mt][v] = mfma_tile<Pr, kTail4>(mt == MT - 1, av, y[dd][v], acc[mt][v]);
-    }
-}
-
 // One direction dd of one point j of the projection: acc[mt][v] += P(mt, qt, 4 dd + j) y[v].
 template <class Pr, int MT, bool kTail4, class L>
 __device__ __forceinline__ void project_dir(const typename Pr::Op* __restrict__ tab, int qt, int j, int dd, int lane,
                                             int g, typename Pr::T (&y)[5], typename Pr::Acc (&acc)[MT][5]) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    if constexpr (kTail4 && Pr::f64) {
-      if (mt == MT - 1) {
-        tail_fma<Pr>(tab + L::proj(mt, qt, 4 * dd + j) * 64 + 16 * g, y, acc[mt]);
-        continue;
-      }
-    }
     const typename Pr::Op av = tab[L::proj(mt, qt, 4 * dd + j) * 64 + lane];
 #pragma unroll
     for (int v = 0; v < 5; ++v) acc[mt][v] = mfma_tile<Pr, kTail4>(mt == MT - 1, av, y[v], acc[mt][v]);
@@ -167,362 +83,428 @@ __device__ __forceinline__ void lift_point(const typename Pr::Op* __restrict__ t
                                            int g, typename Pr::T (&h)[5], typename Pr::Acc (&acc)[MT][5]) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    if constexpr (kTail4 && Pr::f64) {
-      if (mt == MT - 1) {
-        tail_fma<Pr>(tab + L::lift(mt, f, ft, lk) * 64 + 16 * g, h, acc[mt]);
-        continue;
-      }
-    }
     const typename Pr::Op av = tab[L::lift(mt, f, ft, lk) * 64 + lane];
 #pragma unroll
     for (int v = 0; v < 5; ++v) acc[mt][v] = mfma_tile<Pr, kTail4>(mt == MT - 1, av, h[v], acc[mt][v]);
   }
 }
 
-// Accumulate the lift of one face tile: acc[mt][v] += L(mt, f, ft, lk) fh[v][lk].
-template <class Pr, int MT, bool kTail4, class L>
-__device__ __forceinline__ void lift_face(const typename Pr::Op* __restrict__ tab, int f, int ft, int lane, int g,
-                                          typename Pr::T (&fh)[5][4], typename Pr::Acc (&acc)[MT][5]) {
+// Sum the lane groups' shares of the short last tile (FP32, as in the stage kernel).
+template <class Pr>
+__device__ __forceinline__ typename Pr::Acc finish_tail(typename Pr::Acc t) {
+  if constexpr (!Pr::f64) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int lk = 0; lk < 4; ++lk) {
-      if constexpr (kTail4 && Pr::f64) {
-        if (mt == MT - 1) {
-          typename Pr::T fl[5];
-#pragma unroll
-          for (int v = 0; v < 5; ++v) fl[v] = fh[v][lk];
-          tail_fma<Pr>(tab + L::lift(mt, f, ft, lk) * 64 + 16 * g, fl, acc[mt]);
-          continue;
-        }
-      }
-      const typename Pr::Op av = tab[L::lift(mt, f, ft, lk) * 64 + lane];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) acc[mt][v] = mfma_tile<Pr, kTail4>(mt == MT - 1, av, fh[v][lk], acc[mt][v]);
-    }
-}
-
-// Sum the lane groups' shares of the short last tile and place them in the accumulator
-// rows of the precision (as in the stage kernel).
-template <class Pr, int MT, bool kTail4>
-__device__ __forceinline__ void finish_tail(int g, typename Pr::Acc (&acc)[MT][5]) {
-  if constexpr (kTail4) {
-    using T = typename Pr::T;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      T x[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        x[j] = acc[MT - 1][v][j];
-        x[j] += __shfl_xor(x[j], 16);
-        x[j] += __shfl_xor(x[j], 32);
-      }
-      if constexpr (Pr::f64) {
-        acc[MT - 1][v] = typename Pr::Acc{g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : x[3], 0.0, 0.0, 0.0};
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[MT - 1][v][j] = x[j];
-      }
+    for (int j = 0; j < 4; ++j) {
+      float x = t[j];
+      x += __shfl_xor(x, 16);
+      x += __shfl_xor(x, 32);
+      t[j] = x;
     }
   }
+  return t;
 }
 
-// out(variable base + v) = scale * acc (all modes of the element's valid quads; padding 0).
-template <class Pr, int NP, int MT>
-__device__ __forceinline__ void store_tile(char* __restrict__ obase, uint32_t var_bytes, uint32_t quad_bytes, int e,
-                                           int g, double scale, const typename Pr::Acc (&acc)[MT][5]) {
-  using S = typename Pr::S;
-  constexpr int NPQ = npq_of(NP);
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int v = 0; v < 5; ++v)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int mode = 16 * mt + drow(Pr::f64, g, j);
-        if ((mode >> 2) < NPQ) {
-          const double x = mode < NP ? scale * double(acc[mt][v][j]) : 0.0;
-          *reinterpret_cast<S*>(obase + (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
-                                ((size_t)e * 4 + (mode & 3)) * sizeof(S)) = S(x);
-        }
-      }
-}
-
-// BR1 lifting: Z_k = (-int U d_k phi + sum_f int (U- + U+)/2 N_k phi) / |K|.
-// Both terms are linear in the rows of M = |det J| J^-1: the volume integrand's contravariant
-// components are M[d][k] U, and the face normal is N_f,k = sum_d M[d][k] n_f,d with the
-// reference face normals n_0 = (1, 1, 1), n_1 = -e_0, n_2 = -e_1, n_3 = -e_2.  So one
-// interpolation, one set of traces and three reference-direction sums
-//   D_d = sum_q w_q dphi/dxi_d U(q) - sum_f n_f,d int_f Uhat phi
-// serve all three directions: Z_k = -(sum_d M[d][k] D_d) / |K|.
+// One 16-element group per workgroup of four wavefronts, as in the split stage kernel: wavefront
+// w takes face w and the volume point tiles w, w + 4, ... in both passes.
+//   1. Lifting.  Both parts of Z are linear in the rows of M = |det J| J^-1: the volume
+//      integrand's contravariant components are M[d][k] U, and the face normal is N_f,k =
+//      sum_d M[d][k] n_f,d with the reference normals n_0 = (1, 1, 1), n_f = -e_(f-1).  So one
+//      interpolation, one set of traces and three reference-direction sums
+//        D_d = sum_q w_q dphi/dxi_d U(q) - sum_f n_f,d int_f Uhat phi
+//      serve all three directions: Z_k = -(sum_d M[d][k] D_d) / |K|.  The same traces give the
+//      inviscid face fluxes.  The wavefronts' shares of D_d meet in LDS, one direction at a time;
+//      the (mode tile, variable) pairs of Z are dealt out over the wavefronts, which leave them in
+//      LDS as MFMA operands: Z never reaches memory.
+//   2. Fluxes at the volume points and the element's own face points from U and Z (both in LDS).
+// Bound by latency at one or two waves per SIMD (P3 FP64: 64-cycle MFMAs fill a third of the
+// time).  Before, Z was written by one kernel (2.4 KB per element at P3 FP64) and read back for every
+// point tile by a second one, a third added the neighbours' halves and the stage kernel the inviscid
+// part.  Whole stage at 32^3 x 6 elements, before and now, us: FP64 P1 634 -> 551, P2 1170 -> 1139,
+// P3 2484 -> 1866, P4 12679 -> 10550; FP32 416 -> 392, 769 -> 661, 1389 -> 969, 5183 -> 3677; at
+// 384 elements FP64 P1 59 -> 21, P3 187 -> 51.  Tables staged in LDS and workgroups that sweep
+// several groups were slower (P3 FP64 2308: the loop costs registers, 284 bytes per lane spilled).
+//
+// Waves per SIMD: FP64 P2 at two spills 344 bytes per lane and is still the faster one (1139
+// against 1279 us).
 template <int P, class Pr>
-__global__ __launch_bounds__(256, (visc_min_blocks<P, Pr>())) void grad_kernel(ViscArgs a) {
-  TDG_VISC_PROLOGUE
-  char* __restrict__ zout = reinterpret_cast<char*>(a.out);
-  for (int64_t grp = g_begin + wave_x; grp < g_end; grp += waves_x) {
-    const int e = (int)(grp * 16 + col);
-    double Md[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Md[i] = mv.M[i * epad + e];
-    const int fcode = mv.fcode[e];
-    int nbr[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f) nbr[f] = mv.nbr[f * epad + e];
-    Op bc[5][KS];
-    load_operands<Pr, NP, KS>(ubase, var_bytes, (uint32_t)e * 4 * sizeof(S), om, bc);
-    Acc acc[3][MT][5];  // D_d, d = reference direction
-#pragma unroll
-    for (int dd = 0; dd < 3; ++dd)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 5; ++v) acc[dd][mt][v] = Acc{0, 0, 0, 0};
-    // volume: U at the points, projected on the three reference gradients
-#pragma unroll 1
-    for (int qt = 0; qt < QT; ++qt) {
-      Acc d[5];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) d[v] = Acc{0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const Op av = tab[L::interp(qt, s) * 64 + lane];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) d[v] = Pr::mfma(av, bc[v][s], d[v]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int q = 16 * qt + drow(Pr::f64, g, j);
-        T y[5];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) y[v] = q < NQ ? T(d[v][j]) : T(0);
-#pragma unroll
-        for (int dd = 0; dd < 3; ++dd) project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, y, acc[dd]);
-      }
-    }
-    // faces: Uhat = (U- + U+)/2 lifted once per face, into the directions where n_f,d != 0
-#pragma unroll 1
-    for (int f = 0; f < 4; ++f) {
-      T N[3];
-      face_normal<T>(f, Md, N);
-      const int nbf = f == 0 ? nbr[0] : f == 1 ? nbr[1] : f == 2 ? nbr[2] : nbr[3];
-      const int fpl = (fcode >> (2 * f)) & 3;
-      const int en = nbf >= 0 ? nbf : e;
-      Op bn[5][KS];
-      load_operands<Pr, NP, KS>(ubase, var_bytes, (uint32_t)en * 4 * sizeof(S), om, bn);
-#pragma unroll 1
-      for (int ft = 0; ft < FT; ++ft) {
-        Acc dm[5], dp[5];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) dm[v] = dp[v] = Acc{0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          const Op av = tab[L::trace(f, ft, s) * 64 + lane];
-#pragma unroll
-          for (int v = 0; v < 5; ++v) dm[v] = Pr::mfma(av, bc[v][s], dm[v]);
-        }
-#pragma unroll 1
-        for (int c = 0; c < 4; ++c) {
-          const bool mine = nbf >= 0 && fpl == c;
-          if (__any(mine)) {
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-              const Op av = tab[L::trace(c, ft, s) * 64 + lane];
-#pragma unroll
-              for (int v = 0; v < 5; ++v) dp[v] = Pr::mfma(av, mine ? bn[v][s] : Op(0), dp[v]);
-            }
-          }
-        }
-        // n_f,d Uhat: +Uhat for face 0 (all d), -Uhat for face f > 0 (d = f - 1)
-        const T sgn = f == 0 ? T(0.5) : T(-0.5);
-        T fh[5][4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int q = 16 * ft + drow(Pr::f64, g, j);
-          T um[5], up[5];
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            um[v] = T(dm[v][j]);
-            up[v] = T(dp[v][j]);
-          }
-          if (nbf < 0) ghost_state<T>(-nbf, um, N, far, up);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) fh[v][j] = q < NF ? sgn * (um[v] + up[v]) : T(0);
-        }
-#pragma unroll
-        for (int dd = 0; dd < 3; ++dd)
-          if (f == 0 || f == dd + 1) lift_face<Pr, MT, kTail4, L>(tab, f, ft, lane, g, fh, acc[dd]);
-      }
-    }
-    // Z_k = -(sum_d M[d][k] D_d) / |K|
-    const double ivol = mv.inv_vol[e];
-    T Mt[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Mt[i] = T(Md[i]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      Acc z[MT][5];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 5; ++v)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            z[mt][v][j] = Mt[k] * T(acc[0][mt][v][j]) + Mt[3 + k] * T(acc[1][mt][v][j]) + Mt[6 + k] * T(acc[2][mt][v][j]);
-      finish_tail<Pr, MT, kTail4>(g, z);
-      if (e < mv.n_elem) store_tile<Pr, NP, MT>(zout + (size_t)(5 * k) * var_bytes, var_bytes, quad_bytes, e, g, -ivol, z);
-    }
-  }
+constexpr int ns_waves() {
+  return P <= (Pr::f64 ? 2 : 3) ? 2 : 1;
 }
 
-// Viscous residual Rv = -(Vv - Sv) / |K| from U and Z.
-template <int P, class Pr>
-__global__ __launch_bounds__(256, (visc_min_blocks<P, Pr>())) void visc_kernel(ViscArgs a) {
-  TDG_VISC_PROLOGUE
-  const char* __restrict__ zbase = reinterpret_cast<const char*>(a.z);
-  char* __restrict__ obase = reinterpret_cast<char*>(a.out);
-  S* __restrict__ hb = reinterpret_cast<S*>(a.hbuf);
-  const T mu = T(a.mu), kappa = T(a.mu * a.gamma / ((a.gamma - 1.0) * a.prandtl));
-  for (int64_t grp = g_begin + wave_x; grp < g_end; grp += waves_x) {
-    const int e = (int)(grp * 16 + col);
-    const uint32_t eoff = (uint32_t)e * 4 * sizeof(S);
-    double Md[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Md[i] = mv.M[i * epad + e];
-    T Mt[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Mt[i] = T(Md[i]);
-    const int fcode = mv.fcode[e];
-    int nbr[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f) nbr[f] = mv.nbr[f * epad + e];
-    Acc acc[MT][5];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) acc[mt][v] = Acc{0, 0, 0, 0};
-
-    // values of U (w = 0) and Z_k (w = 1 + k) of the element at the points of a tile, by
-    // table t(s), accumulated into out[w][v] (interpolation / trace contractions)
-    auto gather = [&](uint32_t el_off, auto&& table, Acc (&out)[4][5]) {
-      // the element's own operands are the same in every tile: an opaque offset keeps their
-      // loads inside the loop (hoisted out, 20 variables x KS operands stay live and spill)
-      asm volatile("" : "+v"(el_off));
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const char* src = w == 0 ? ubase : zbase + (size_t)(5 * (w - 1)) * var_bytes;
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          Op b[1][KS];
-          load_operands<Pr, NP, KS, 1>(src + (size_t)v * var_bytes, var_bytes, el_off, om, b);
-#pragma unroll
-          for (int s = 0; s < KS; ++s) {
-            const Op av = tab[table(s) * 64 + lane];
-            out[w][v] = Pr::mfma(av, b[0][s], out[w][v]);
-          }
-        }
-      }
-    };
-    auto zero = [&](Acc (&out)[4][5]) {
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-#pragma unroll
-        for (int v = 0; v < 5; ++v) out[w][v] = Acc{0, 0, 0, 0};
-    };
-    auto point = [&](const Acc (&vals)[4][5], int j, T (&U)[5], T (&Z)[3][5]) {
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        U[v] = T(vals[0][v][j]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) Z[k][v] = T(vals[1 + k][v][j]);
-      }
-    };
-
-    // ---------------- volume: Vv = int F_v(U, Z) . grad phi
-#pragma unroll 1
-    for (int qt = 0; qt < QT; ++qt) {
-      Acc vals[4][5];
-      zero(vals);
-      gather(eoff, [&](int s) { return L::interp(qt, s); }, vals);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int q = 16 * qt + drow(Pr::f64, g, j);
-        T U[5], Z[3][5], Fv[3][5];
-        point(vals, j, U, Z);
-        visc_flux<T>(U, Z, gm1, mu, kappa, Fv);
-#pragma unroll
-        for (int dd = 0; dd < 3; ++dd) {
-          T y[5];
-#pragma unroll
-          for (int v = 0; v < 5; ++v)
-            y[v] = q < NQ ? Mt[3 * dd] * Fv[0][v] + Mt[3 * dd + 1] * Fv[1][v] + Mt[3 * dd + 2] * Fv[2][v] : T(0);
-          project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, y, acc);
-        }
-      }
-    }
-
-    // ---------------- faces: Sv = sum_f int (F_v- + F_v+)/2 . N phi, the own half here
-#pragma unroll 1
-    for (int f = 0; f < 4; ++f) {
-      T N[3];
-      face_normal<T>(f, Md, N);
-      const int nbf = f == 0 ? nbr[0] : f == 1 ? nbr[1] : f == 2 ? nbr[2] : nbr[3];
-      const int fpl = (fcode >> (2 * f)) & 3;
-#pragma unroll 1
-      for (int ft = 0; ft < FT; ++ft) {
-        // own half (and, on a boundary face, the ghost half with Z+ = Z-)
-        {
-          Acc vals[4][5];
-          zero(vals);
-          gather(eoff, [&](int s) { return L::trace(f, ft, s); }, vals);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int q = 16 * ft + drow(Pr::f64, g, j);
-            T U[5], Z[3][5], Fv[3][5], h[5];
-            point(vals, j, U, Z);
-            visc_flux<T>(U, Z, gm1, mu, kappa, Fv);
-#pragma unroll
-            for (int v = 0; v < 5; ++v) h[v] = Fv[0][v] * N[0] + Fv[1][v] * N[1] + Fv[2][v] * N[2];
-            if (nbf < 0) {
-              T Ub[5];
-              ghost_state<T>(-nbf, U, N, far, Ub);
-              visc_flux<T>(Ub, Z, gm1, mu, kappa, Fv);
-#pragma unroll
-              for (int v = 0; v < 5; ++v) h[v] += Fv[0][v] * N[0] + Fv[1][v] * N[1] + Fv[2][v] * N[2];
-            }
-#pragma unroll
-            for (int v = 0; v < 5; ++v) h[v] = q < NF ? T(0.5) * h[v] : T(0);
-            lift_point<Pr, MT, kTail4, L>(tab, f, ft, j, lane, g, h, acc);
-            // the own half of an interior face, for the neighbour's side of this face: per
-            // (element, face, variable) 16 FT values, the point held in register j of lane
-            // group g at 16 ft + 4 g + j, so that a reader's lane gets its four points at once
-            if (nbf >= 0 && e < mv.n_elem) {
-#pragma unroll
-              for (int v = 0; v < 5; ++v) hb[((((size_t)e * 4 + f) * 5 + v) * FT + ft) * 16 + 4 * g + j] = S(h[v]);
-            }
-          }
-        }
-      }
-    }
-    finish_tail<Pr, MT, kTail4>(g, acc);
-    // acc = Vv - Sv (the lift tables carry the face integral's minus sign): Rv = -acc / |K|
-    if (e < mv.n_elem) store_tile<Pr, NP, MT>(obase, var_bytes, quad_bytes, e, g, -mv.inv_vol[e], acc);
-  }
-}
-
-// Neighbour halves of the viscous face term: Rv += -(sum_f int_f (F_v+ . N / 2) phi) / |K|
-// (with the lift tables' sign), where F_v+ . N / 2 at our face point q is minus the
-// neighbour's stored own half at point q of its face f+.
-// Light kernel: the lift tables are read through the caches (no LDS staging), so several
-// workgroups share a CU.
-template <int P, class Pr>
-__global__ __launch_bounds__(256) void visc_nbr_kernel(ViscArgs a) {
+template <int P, class Pr, bool kRoe>
+__global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a) {
   using O = Ord<P>;
   using L = Layout<P, 1>;
   using S = typename Pr::S;
   using T = typename Pr::T;
   using Op = typename Pr::Op;
   using Acc = typename Pr::Acc;
-  constexpr int NP = O::NP, NF = O::NF, MT = O::MT, FT = O::FT;
+  constexpr int NP = O::NP, NQ = O::NQ, NF = O::NF, MT = O::MT, QT = O::QT, FT = O::FT, KS = L::KS;
+  constexpr int NPQ = npq_of(NP), W = 4, NPAIR = MT * 5;
+  constexpr bool kTail4 = NP - 16 * (MT - 1) <= 4;
+  // the wavefronts' accumulators of one reduction; Z's operands between the two passes
+  constexpr size_t kRed = sizeof(Acc) * W * NPAIR * 64, kZ = sizeof(Op) * 15 * KS * 64;
+  __shared__ __align__(32) char lds_raw[kRed > kZ ? kRed : kZ];
+  __shared__ Op lds_u[5 * KS * 64];
+  Acc* const red = reinterpret_cast<Acc*>(lds_raw);
+  Op* const lz = reinterpret_cast<Op*>(lds_raw);
+  const Op* __restrict__ tab = reinterpret_cast<const Op*>(a.tab);
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const MeshView& mv = a.mesh;
+  const int64_t epad = mv.epad;
+  // each XCD owns a contiguous eighth of the groups (workgroups go round-robin over the XCDs)
+  const int64_t ngroups = epad / 16, chunk = (ngroups + 7) / 8;
+  const int64_t grp = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  if (grp >= ngroups) return;
+  const uint32_t quad_bytes = (uint32_t)(epad * 4 * sizeof(S));
+  const uint32_t var_bytes = quad_bytes * NPQ;
+  const char* __restrict__ ubase = reinterpret_cast<const char*>(a.u);
+  S* __restrict__ hb = reinterpret_cast<S*>(a.hbuf);
+  const T gamma = T(a.gamma), gm1 = T(a.gamma - 1.0);
+  const T mu = T(a.mu), kappa = T(a.mu * a.gamma / ((a.gamma - 1.0) * a.prandtl));
+  T far[5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) far[v] = T(a.far[v]);
+  OperandMap<Pr, NP, KS> om;
+  om.init(g, quad_bytes);
+  // leave x (plus y where `on`) in red / the sum of what the wavefronts left there
+  auto share = [&](const Acc (&x)[MT][5], const Acc (&y)[MT][5], bool on) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int v = 0; v < 5; ++v)
+        red[(w * NPAIR + mt * 5 + v) * 64 + lane] = on ? x[mt][v] + y[mt][v] : x[mt][v];
+    __syncthreads();
+  };
+  auto shared_sum = [&](int mt, int v) {
+    Acc t = red[(mt * 5 + v) * 64 + lane];
+#pragma unroll
+    for (int x = 1; x < W; ++x) t += red[(x * NPAIR + mt * 5 + v) * 64 + lane];
+    return t;
+  };
+
+
+  const int e = (int)(grp * 16 + col);
+  const bool live = e < mv.n_elem;
+  const uint32_t eoff = (uint32_t)e * 4 * sizeof(S);
+  double Md[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) Md[i] = mv.M[i * epad + e];
+  T Mt[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) Mt[i] = T(Md[i]);
+  const double ivol = mv.inv_vol[e];
+  // always true, but a branch to the compiler: without it the face's loads and fluxes are
+  // scheduled into the neighbouring phases (P3 FP64 then spills 176 bytes per lane)
+  const bool face = w < 4;
+  const int wf = face ? w : 0;
+  const int nbf = mv.nbr[wf * epad + e];
+  const int fpl = (mv.fcode[e] >> (2 * wf)) & 3;
+  // the element's own operands, shared by the wavefronts
+  for (int v = w; v < 5; v += W) {
+    Op b[1][KS];
+    load_operands<Pr, NP, KS, 1>(ubase + (size_t)v * var_bytes, var_bytes, eoff, om, b);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) lds_u[(v * KS + s) * 64 + lane] = b[0][s];
+  }
+  Op bn[5][KS];
+  if (face) load_operands<Pr, NP, KS>(ubase, var_bytes, (uint32_t)(nbf >= 0 ? nbf : e) * 4 * sizeof(S), om, bn);
+  T N[3];
+  face_normal<T>(wf, Md, N);
+  __syncthreads();
+
+  // U at the points of a tile by table t(s)
+  auto own_u = [&](auto&& table, Acc (&d)[5]) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) d[v] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const Op av = tab[table(s) * 64 + lane];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) d[v] = Pr::mfma(av, lds_u[(v * KS + s) * 64 + lane], d[v]);
+    }
+  };
+
+  Acc lift[MT][5];  // face w's share of D_(w-1) (face 0: of every D_d)
+  Acc acc[MT][5];   // (V - S) - (Vv - Sv)
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int v = 0; v < 5; ++v) lift[mt][v] = acc[mt][v] = Acc{0, 0, 0, 0};
+  // up to P3 a wavefront has one tile of each kind and keeps the face's inviscid flux and the
+  // volume points' U until pass 2; at P4 it lifts the flux at once and interpolates U again
+  constexpr bool kKeep = P <= 3;
+  T fi[4][5];
+
+  // ---------------- pass 1: face w, Uhat = (U- + U+)/2 and the inviscid flux
+  if (face) {
+    const T nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
+#pragma unroll 1
+    for (int ft = 0; ft < FT; ++ft) {
+      Acc dm[5], dp[5];
+      own_u([&](int s) { return L::trace(w, ft, s); }, dm);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) dp[v] = Acc{0, 0, 0, 0};
+#pragma unroll 1
+      for (int c = 0; c < 4; ++c) {
+        const bool mine = nbf >= 0 && fpl == c;
+        if (__any(mine)) {
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            const Op av = tab[L::trace(c, ft, s) * 64 + lane];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) dp[v] = Pr::mfma(av, mine ? bn[v][s] : Op(0), dp[v]);
+          }
+        }
+      }
+      // n_f,d Uhat: +Uhat for face 0 (all d), -Uhat for face f > 0 (d = f - 1)
+      const T sgn = w == 0 ? T(0.5) : T(-0.5);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int q = 16 * ft + drow(Pr::f64, g, j);
+        T um[5], up[5], uh[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          um[v] = T(dm[v][j]);
+          up[v] = T(dp[v][j]);
+        }
+        if (nbf < 0) ghost_state<T>(-nbf, um, N, far, up);
+        num_flux<kRoe, T>(um, up, N, nn, gamma, fi[j]);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          uh[v] = q < NF ? sgn * (um[v] + up[v]) : T(0);
+          fi[j][v] = q < NF ? fi[j][v] : T(0);
+        }
+        lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, uh, lift);
+        if constexpr (!kKeep) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+      }
+    }
+  }
+  // ---------------- pass 1: U at the volume points of this wavefront's tiles
+  constexpr int NT = (QT + W - 1) / W;
+  Acc du1[NT][5];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int qt = w + W * t;
+    if (qt >= QT) continue;
+    own_u([&](int s) { return L::interp(qt, s); }, du1[t]);
+    // points past the rule count as zero
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (16 * qt + drow(Pr::f64, g, j) >= NQ) du1[t][v][j] = 0;
+  }
+
+  // ---------------- Z_k = -(sum_d M[d][k] D_d) / |K|, pairs 5 mt + v = w (mod 4) per wavefront
+  constexpr int NVW = (5 + W - 1) / W;
+  auto pair_v = [&](int mt, int i) {
+    const int v = w - 5 * mt % W;
+    return (v < 0 ? v + W : v) + W * i;
+  };
+  {
+    Acc z[MT][NVW][3];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < NVW; ++i) z[mt][i][0] = z[mt][i][1] = z[mt][i][2] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int dd = 0; dd < 3; ++dd) {
+      // this wavefront's share of D_dd: its volume tiles, and its face where n_f,dd is not zero
+      const bool on = w == 0 || w == dd + 1;
+      Acc D[MT][5];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) D[mt][v] = Acc{0, 0, 0, 0};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (w + W * t >= QT) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          T y[5];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) y[v] = T(du1[t][v][j]);
+          project_dir<Pr, MT, kTail4, L>(tab, w + W * t, j, dd, lane, g, y, D);
+        }
+      }
+      if (dd > 0) __syncthreads();  // the previous direction's shares are read
+      share(D, lift, on);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < NVW; ++i) {
+          const int v = pair_v(mt, i);
+          if (v >= 5) continue;
+          const Acc t = shared_sum(mt, v);
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[mt][i][k][j] = fmaT(Mt[3 * dd + k], T(t[j]), T(z[mt][i][k][j]));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < NVW; ++i) {
+        const int v = pair_v(mt, i);
+        if (v >= 5) continue;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          T x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = -T(ivol) * T(z[mt][i][k][j]);
+          Op* const zk = lz + (5 * k + v) * KS * 64;
+          if constexpr (Pr::f64) {
+            // register j of lane group g: mode 16 mt + g + 4 j, operand step 4 mt + j of this lane
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (4 * mt + j < KS) zk[(4 * mt + j) * 64 + lane] = x[j];
+          } else if (kTail4 && mt == MT - 1) {
+            // the lane groups' shares of modes 16 mt .. + 3: operand step 4 mt, mode 16 mt + g
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              x[j] += __shfl_xor(x[j], 16);
+              x[j] += __shfl_xor(x[j], 32);
+            }
+            zk[4 * mt * 64 + lane] = g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : x[3];
+          } else if (4 * mt + g < KS) {
+            // register j of lane group g: mode 16 mt + 4 g + j, step 4 mt + g of lane group j
+#pragma unroll
+            for (int j = 0; j < 4; ++j) zk[(4 * mt + g) * 64 + 16 * j + col] = x[j];
+          }
+        }
+      }
+    __syncthreads();
+  }
+
+  // ---------------- pass 2: U and Z at the points of a tile by table t(s)
+  auto z_values = [&](auto&& table, Acc (&dz)[3][5]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) dz[k][v] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const Op av = tab[table(s) * 64 + lane];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) dz[k][v] = Pr::mfma(av, lz[((5 * k + v) * KS + s) * 64 + lane], dz[k][v]);
+    }
+  };
+  auto point = [&](const Acc (&du)[5], const Acc (&dz)[3][5], int j, T (&U)[5], T (&Z)[3][5]) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      U[v] = T(du[v][j]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) Z[k][v] = T(dz[k][v][j]);
+    }
+  };
+#pragma unroll 1
+  for (int qt = w; qt < QT; qt += W) {
+    Acc du[5], dz[3][5];
+    if constexpr (kKeep) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) du[v] = du1[0][v];
+    } else {
+      own_u([&](int s) { return L::interp(qt, s); }, du);
+    }
+    z_values([&](int s) { return L::interp(qt, s); }, dz);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = 16 * qt + drow(Pr::f64, g, j);
+      T U[5], Z[3][5], Fv[3][5], yy[3][5];
+      point(du, dz, j, U, Z);
+      visc_flux<T>(U, Z, gm1, mu, kappa, Fv);
+      contra_flux<T>(U, Mt, gm1, yy);
+#pragma unroll
+      for (int dd = 0; dd < 3; ++dd) {
+        T y[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v)
+          y[v] = q < NQ ? yy[dd][v] - (Mt[3 * dd] * Fv[0][v] + Mt[3 * dd + 1] * Fv[1][v] + Mt[3 * dd + 2] * Fv[2][v])
+                        : T(0);
+        project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, y, acc);
+      }
+    }
+  }
+  // face w: the own half (and, on a boundary face, the ghost half with Z+ = Z-)
+#pragma unroll 1
+  for (int ft = face ? 0 : FT; ft < FT; ++ft) {
+    Acc du[5], dz[3][5];
+    own_u([&](int s) { return L::trace(w, ft, s); }, du);
+    z_values([&](int s) { return L::trace(w, ft, s); }, dz);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = 16 * ft + drow(Pr::f64, g, j);
+      T U[5], Z[3][5], Fv[3][5], h[5];
+      point(du, dz, j, U, Z);
+      visc_flux<T>(U, Z, gm1, mu, kappa, Fv);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) h[v] = Fv[0][v] * N[0] + Fv[1][v] * N[1] + Fv[2][v] * N[2];
+      if (nbf < 0) {
+        T Ub[5];
+        ghost_state<T>(-nbf, U, N, far, Ub);
+        visc_flux<T>(Ub, Z, gm1, mu, kappa, Fv);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) h[v] += Fv[0][v] * N[0] + Fv[1][v] * N[1] + Fv[2][v] * N[2];
+      }
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        h[v] = q < NF ? T(0.5) * h[v] : T(0);
+        fi[j][v] = kKeep ? fi[j][v] - h[v] : -h[v];
+      }
+      lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+      // the own half of an interior face, for the neighbour's side of this face: per
+      // (element, face, variable) 16 FT values, the point held in register j of lane
+      // group g at 16 ft + 4 g + j, so that a reader's lane gets its four points at once
+      if (nbf >= 0 && live) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) hb[((((size_t)e * 4 + w) * 5 + v) * FT + ft) * 16 + 4 * g + j] = S(h[v]);
+      }
+    }
+  }
+
+  // ---------------- the residual without the neighbours' halves
+  __syncthreads();
+  share(acc, acc, false);
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int i = 0; i < NVW; ++i) {
+      const int v = pair_v(mt, i);
+      if (v >= 5) continue;
+      Acc t = shared_sum(mt, v);
+      if (kTail4 && mt == MT - 1) t = finish_tail<Pr>(t);
+      if (!live) continue;
+      char* const ob = reinterpret_cast<char*>(a.out) + (size_t)v * var_bytes + eoff;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int mode = 16 * mt + drow(Pr::f64, g, j);
+        if ((mode >> 2) < NPQ)
+          *reinterpret_cast<S*>(ob + (uint32_t)(mode >> 2) * quad_bytes + (mode & 3) * sizeof(S)) =
+              S(mode < NP ? ivol * double(t[j]) : 0.0);
+      }
+    }
+}
+
+// Neighbour halves of the viscous face term, then the stage's update: R = R_own - (sum_f int_f
+// (F_v+ . N / 2) phi) / |K| (with the lift tables' sign), where F_v+ . N / 2 at our face point q is
+// minus the neighbour's stored own half at point q of its face f+; R is stored or U_out =
+// alpha U0 + (1 - alpha)(U_in + dt R).  Bound by its reads (6 KB per element at P3 FP64): a light
+// kernel, the lift tables read through the caches, several workgroups per CU.
+template <int P, class Pr>
+__global__ __launch_bounds__(256) void ns_update_kernel(ViscArgs a) {
+  using O = Ord<P>;
+  using L = Layout<P, 1>;
+  using S = typename Pr::S;
+  using T = typename Pr::T;
+  using Op = typename Pr::Op;
+  using Acc = typename Pr::Acc;
+  constexpr int NP = O::NP, MT = O::MT, FT = O::FT;
   constexpr int NPQ = npq_of(NP);
   constexpr bool kTail4 = NP - 16 * (MT - 1) <= 4;
   const Op* __restrict__ tab = reinterpret_cast<const Op*>(a.tab);
@@ -531,19 +513,13 @@ __global__ __launch_bounds__(256) void visc_nbr_kernel(ViscArgs a) {
   const int64_t epad = mv.epad;
   const uint32_t quad_bytes = (uint32_t)(epad * 4 * sizeof(S));
   const uint32_t var_bytes = quad_bytes * NPQ;
-  const int nblk = gridDim.x;
-  const int nwb = blockDim.x >> 6;
-  const int nx = (nblk % 8 == 0) ? 8 : 1;
-  const int xcd = blockIdx.x % nx;
-  const int64_t waves_x = (int64_t)(nblk / nx) * nwb;
-  const int64_t wave_x = (int64_t)(blockIdx.x / nx) * nwb + (threadIdx.x >> 6);
-  const int64_t ngroups = epad / 16;
-  const int64_t chunk = (ngroups + nx - 1) / nx;
-  const int64_t g_begin = xcd * chunk;
-  const int64_t g_end = g_begin + chunk < ngroups ? g_begin + chunk : ngroups;
+  const int64_t ngroups = epad / 16, nblk8 = gridDim.x / 8;
+  const int64_t chunk = (ngroups + 7) / 8;
+  const int64_t first = (blockIdx.x % 8) * chunk;
+  const int64_t last = first + chunk < ngroups ? first + chunk : ngroups;
   const S* __restrict__ hb = reinterpret_cast<const S*>(a.hbuf);
-  char* __restrict__ obase = reinterpret_cast<char*>(a.out);
-  for (int64_t grp = g_begin + wave_x; grp < g_end; grp += waves_x) {
+  const double dt = a.dt_dev ? *a.dt_dev : a.dt;
+  for (int64_t grp = first + (int64_t)(blockIdx.x / 8) * 4 + (threadIdx.x >> 6); grp < last; grp += nblk8 * 4) {
     const int e = (int)(grp * 16 + col);
     const int fcode = mv.fcode[e];
     int nbr[4];
@@ -569,15 +545,18 @@ __global__ __launch_bounds__(256) void visc_nbr_kernel(ViscArgs a) {
           // the neighbour's values at points 16 ft + drow(g, j), j = 0..3 (zero past N_f)
           const s4_t x = *reinterpret_cast<const s4_t*>(hb + rec + ((size_t)v * FT + ft) * 16 + 4 * g);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) h[j][v] = nbf >= 0 ? -T(x[j]) : T(0);
+          for (int j = 0; j < 4; ++j) h[j][v] = nbf >= 0 ? T(x[j]) : T(0);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) lift_point<Pr, MT, kTail4, L>(tab, f, ft, j, lane, g, h[j], acc);
       }
     }
-    finish_tail<Pr, MT, kTail4>(g, acc);
+    if constexpr (kTail4) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) acc[MT - 1][v] = finish_tail<Pr>(acc[MT - 1][v]);
+    }
     if (e < mv.n_elem) {
-      const double scale = -mv.inv_vol[e];
+      const double ivol = mv.inv_vol[e];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -585,18 +564,34 @@ __global__ __launch_bounds__(256) void visc_nbr_kernel(ViscArgs a) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int mode = 16 * mt + drow(Pr::f64, g, j);
-            if (mode < NP) {
-              S* o = reinterpret_cast<S*>(obase + (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
-                                          ((size_t)e * 4 + (mode & 3)) * sizeof(S));
-              *o = S(double(*o) + scale * double(acc[mt][v][j]));
+            if ((mode >> 2) < NPQ) {
+              const size_t o = (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
+                               ((size_t)e * 4 + (mode & 3)) * sizeof(S);
+              auto at = [&](const void* p) { return double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + o)); };
+              double r = at(a.r_own) + ivol * double(acc[mt][v][j]);
+              if (a.rk) {
+                const double u0 = a.alpha != 0.0 ? at(a.u0) : 0.0;
+                r = a.alpha * u0 + (1.0 - a.alpha) * (at(a.u) + dt * r);
+              }
+              *reinterpret_cast<S*>(reinterpret_cast<char*>(a.out) + o) = S(mode < NP ? r : 0.0);
             }
           }
     }
   }
 }
 
-template <class K>
-hipError_t launch_visc_grid(K kern, const ViscArgs& a, hipStream_t stream) {
+template <int P, class Pr>
+hipError_t launch_ns_impl(const ViscArgs& a, hipStream_t stream) {
+  const int64_t ngroups = a.mesh.epad / 16;
+  auto kern = a.flux == 1 ? ns_kernel<P, Pr, true> : ns_kernel<P, Pr, false>;
+  // one group per workgroup, the same number of workgroups on every XCD
+  hipLaunchKernelGGL(kern, dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int P, class Pr>
+hipError_t launch_ns_update_impl(const ViscArgs& a, hipStream_t stream) {
+  auto kern = ns_update_kernel<P, Pr>;
   int per_cu = 0;
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
   if (err != hipSuccess) return err;
@@ -604,46 +599,26 @@ hipError_t launch_visc_grid(K kern, const ViscArgs& a, hipStream_t stream) {
   int dev = 0, ncu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const int64_t ngroups = a.mesh.epad / 16;
-  int64_t want = (ngroups + 3) / 4;
-  int64_t fill = (int64_t)ncu * per_cu;
-  int64_t nblk = want < fill ? want : fill;
-  if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-  if (nblk >= 8) nblk -= nblk % 8;
-  if (nblk < 1) nblk = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
+  const int64_t want = (a.mesh.epad / 16 + 3) / 4, fill = (int64_t)ncu * per_cu;
+  const int64_t nblk = want < fill ? want : fill;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
-#undef TDG_VISC_PROLOGUE
-
 }  // namespace
 
-hipError_t launch_grad(int p, int prec, const ViscArgs& a, hipStream_t stream) {
-#define TDG_CASE(PP)                                                                            \
-  if (p == PP)                                                                                  \
-    return prec == 1 ? launch_visc_grid(grad_kernel<PP, PrecF32>, a, stream)                   \
-                     : launch_visc_grid(grad_kernel<PP, PrecF64>, a, stream);
+hipError_t launch_ns(int p, int prec, const ViscArgs& a, hipStream_t stream) {
+#define TDG_CASE(PP) \
+  if (p == PP) return prec == 1 ? launch_ns_impl<PP, PrecF32>(a, stream) : launch_ns_impl<PP, PrecF64>(a, stream);
   TDG_CASE(1) TDG_CASE(2) TDG_CASE(3) TDG_CASE(4)
 #undef TDG_CASE
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_visc(int p, int prec, const ViscArgs& a, hipStream_t stream) {
-#define TDG_CASE(PP)                                                                            \
-  if (p == PP)                                                                                  \
-    return prec == 1 ? launch_visc_grid(visc_kernel<PP, PrecF32>, a, stream)                   \
-                     : launch_visc_grid(visc_kernel<PP, PrecF64>, a, stream);
-  TDG_CASE(1) TDG_CASE(2) TDG_CASE(3) TDG_CASE(4)
-#undef TDG_CASE
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_visc_nbr(int p, int prec, const ViscArgs& a, hipStream_t stream) {
-#define TDG_CASE(PP)                                                                            \
-  if (p == PP)                                                                                  \
-    return prec == 1 ? launch_visc_grid(visc_nbr_kernel<PP, PrecF32>, a, stream)               \
-                     : launch_visc_grid(visc_nbr_kernel<PP, PrecF64>, a, stream);
+hipError_t launch_ns_update(int p, int prec, const ViscArgs& a, hipStream_t stream) {
+#define TDG_CASE(PP)                                                                   \
+  if (p == PP)                                                                         \
+    return prec == 1 ? launch_ns_update_impl<PP, PrecF32>(a, stream) : launch_ns_update_impl<PP, PrecF64>(a, stream);
   TDG_CASE(1) TDG_CASE(2) TDG_CASE(3) TDG_CASE(4)
 #undef TDG_CASE
   return hipErrorInvalidValue;
