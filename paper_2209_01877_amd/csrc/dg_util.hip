@@ -7,59 +7,137 @@ namespace tetdg {
 
 namespace {
 
-template <class S>
-__global__ void set_state_kernel(MeshView m, int np, const double* __restrict__ user, S* __restrict__ out) {
-  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (n >= m.epad) return;
-  const int64_t src = m.perm[n];
-  for (int v = 0; v < 5; ++v)
-    for (int i = 0; i < 4 * npq_of(np); ++i)
-      out[sidx(v, i, n, m.epad, npq_of(np))] = i < np ? S(user[(src * 5 + v) * np + i]) : S(0);
-}
+// Layout conversion between the caller's records ([E][5][N_p] doubles, caller's order) and the
+// internal quads, 32 consecutive internal elements per workgroup through LDS, so that both sides
+// move whole lines: a record is 40 N_p contiguous bytes, a (variable, quad) plane of the tile 32
+// contiguous quads.  (One thread per element, striding over either side, moved 1.2 TB/s.)  An LDS
+// record is 5 N_p + 1 doubles.
+constexpr int kTileE = 32;
 
-template <class S>
-__global__ void get_state_kernel(MeshView m, int np, const S* __restrict__ in, double* __restrict__ user) {
-  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (n >= m.n_elem) return;
-  const int64_t dst = m.perm[n];
-  for (int v = 0; v < 5; ++v)
-    for (int i = 0; i < np; ++i) user[(dst * 5 + v) * np + i] = double(in[sidx(v, i, n, m.epad, npq_of(np))]);
-}
-
-__global__ void volume_points_kernel(MeshView m, int nq, RefView r, double* __restrict__ xyz) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m.n_elem * nq) return;
-  const int64_t n = t / nq;
-  const int q = (int)(t % nq);
-  const int64_t dst = m.perm[n];
-  for (int d = 0; d < 3; ++d) {
-    double x = m.x0j[d * m.epad + n];
-    for (int c = 0; c < 3; ++c) x += m.x0j[(3 + 3 * d + c) * m.epad + n] * r.qx[3 * q + c];
-    xyz[(dst * nq + q) * 3 + d] = x;
+template <int P, class S>
+__global__ __launch_bounds__(256) void set_state_kernel(MeshView m, const double* __restrict__ user,
+                                                        S* __restrict__ out) {
+  constexpr int NP = Ord<P>::NP, NPQ = npq_of(NP), REC = 5 * NP;
+  __shared__ double tile[kTileE * (REC + 1)];
+  const int64_t e0 = (int64_t)blockIdx.x * kTileE;
+  __shared__ int perm[kTileE];
+  if (threadIdx.x < kTileE) perm[threadIdx.x] = m.perm[e0 + threadIdx.x];
+  __syncthreads();
+  // all of a thread's reads are issued before the first LDS write
+  constexpr int NIT = (kTileE * REC + 255) / 256;
+  double x[NIT];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int i = (int)threadIdx.x + 256 * it;
+    if (i < kTileE * REC) x[it] = user[(int64_t)perm[i / REC] * REC + i % REC];
+  }
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int i = (int)threadIdx.x + 256 * it;
+    if (i < kTileE * REC) tile[i / REC * (REC + 1) + i % REC] = x[it];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 5 * NPQ * kTileE * 4; i += 256) {
+    const int el = (i / 4) % kTileE, vk = i / (4 * kTileE), mode = 4 * (vk % NPQ) + i % 4;
+    out[((int64_t)vk * m.epad + e0 + el) * 4 + i % 4] =
+        mode < NP ? S(tile[el * (REC + 1) + vk / NPQ * NP + mode]) : S(0);
   }
 }
 
-// c_i = (1/|K|) int_K U phi_i = 6 sum_q w_q U(x_q) phi_i(xi_q); one thread per (element, mode)
-template <class S>
-__global__ void project_kernel(MeshView m, int np, int nq, RefView r, double gamma, const double* __restrict__ prim,
-                               S* __restrict__ out) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m.epad * np) return;
-  const int64_t n = t / np;
-  const int i = (int)(t % np);
-  const int64_t src = m.perm[n];
-  double acc[5] = {0, 0, 0, 0, 0};
-  for (int q = 0; q < nq; ++q) {
-    const double* pq = prim + (src * nq + q) * 5;
-    const double rho = pq[0], u = pq[1], v = pq[2], w = pq[3], p = pq[4];
-    const double U[5] = {rho, rho * u, rho * v, rho * w, p / (gamma - 1.0) + 0.5 * rho * (u * u + v * v + w * w)};
-    const double wb = 6.0 * r.qw[q] * r.B[q * np + i];
-    for (int c = 0; c < 5; ++c) acc[c] += wb * U[c];
+template <int P, class S>
+__global__ __launch_bounds__(256) void get_state_kernel(MeshView m, const S* __restrict__ in,
+                                                        double* __restrict__ user) {
+  constexpr int NP = Ord<P>::NP, NPQ = npq_of(NP), REC = 5 * NP;
+  __shared__ double tile[kTileE * (REC + 1)];
+  const int64_t e0 = (int64_t)blockIdx.x * kTileE;
+  for (int i = threadIdx.x; i < 5 * NPQ * kTileE * 4; i += 256) {
+    const int el = (i / 4) % kTileE, vk = i / (4 * kTileE), mode = 4 * (vk % NPQ) + i % 4;
+    const S x = in[((int64_t)vk * m.epad + e0 + el) * 4 + i % 4];
+    if (mode < NP) tile[el * (REC + 1) + vk / NPQ * NP + mode] = double(x);
   }
-  for (int c = 0; c < 5; ++c) out[sidx(c, i, n, m.epad, npq_of(np))] = S(acc[c]);
-  if (i == 0)  // zero the padding modes of the last quad
-    for (int c = 0; c < 5; ++c)
-      for (int k = np; k < 4 * npq_of(np); ++k) out[sidx(c, k, n, m.epad, npq_of(np))] = S(0);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kTileE * REC; i += 256) {
+    const int el = i / REC, k = i % REC;
+    if (e0 + el < m.n_elem) user[(int64_t)m.perm[e0 + el] * REC + k] = tile[el * (REC + 1) + k];
+  }
+}
+
+// Points x = X0 + J xi_q, 32 elements per workgroup: their maps are staged in LDS, and every
+// wavefront writes an element's 3 N_q coordinates as one run.
+template <int P>
+__global__ __launch_bounds__(256) void volume_points_kernel(MeshView m, RefView r, double* __restrict__ xyz) {
+  constexpr int NQ = Ord<P>::NQ;
+  __shared__ double map[12 * kTileE], xi[3 * NQ];
+  const int64_t e0 = (int64_t)blockIdx.x * kTileE;
+  for (int i = threadIdx.x; i < 12 * kTileE; i += 256) map[i] = m.x0j[(i / kTileE) * m.epad + e0 + i % kTileE];
+  for (int i = threadIdx.x; i < 3 * NQ; i += 256) xi[i] = r.qx[i];
+  __syncthreads();
+  for (int el = threadIdx.x >> 6; el < kTileE; el += 4) {
+    if (e0 + el >= m.n_elem) break;
+    double* const dst = xyz + (int64_t)m.perm[e0 + el] * (3 * NQ);
+    for (int i = threadIdx.x & 63; i < 3 * NQ; i += 64) {
+      const int q = i / 3, d = i % 3;
+      double x = map[d * kTileE + el];
+      for (int c = 0; c < 3; ++c) x += map[(3 + 3 * d + c) * kTileE + el] * xi[3 * q + c];
+      dst[i] = x;
+    }
+  }
+}
+
+// fp64 MFMA column tiles as in the stage kernel (16 elements per wavefront), for every state type.
+typedef double util_d4 __attribute__((ext_vector_type(4)));
+
+// c_i = (1/|K|) int_K U phi_i = 6 sum_q w_q U(x_q) phi_i(xi_q): rows = modes, k = points (lane group
+// g holds point 4 s + g of step s and converts it once), the short last mode tile on the blocked
+// 4x4x4 MFMA.  (One thread per (element, mode) converted every point N_p times.)
+template <int P, class S>
+__global__ __launch_bounds__(256) void project_kernel(MeshView m, RefView r, double gamma,
+                                                      const double* __restrict__ prim, S* __restrict__ out) {
+  constexpr int NP = Ord<P>::NP, NQ = Ord<P>::NQ, MT = Ord<P>::MT, NPQ = npq_of(NP), QS = (NQ + 3) / 4;
+  constexpr bool kTail4 = NP - 16 * (MT - 1) <= 4;
+  __shared__ double tab[MT * QS * 64];
+  for (int i = threadIdx.x; i < MT * QS * 64; i += 256) {
+    const int l = i % 64, st = i / 64 % QS, mt = i / 64 / QS;
+    const int row = kTail4 && mt == MT - 1 ? l % 4 : l % 16, mode = 16 * mt + row, q = 4 * st + l / 16;
+    tab[i] = mode < NP && q < NQ ? 6.0 * r.qw[q] * r.B[q * NP + mode] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int64_t ngroups = m.epad / 16, stride = (int64_t)gridDim.x * 4;
+  for (int64_t grp = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); grp < ngroups; grp += stride) {
+    const int64_t e = grp * 16 + col;
+    const double* const src = prim + (int64_t)m.perm[e] * (5 * NQ);
+    util_d4 acc[MT][5];
+    for (int mt = 0; mt < MT; ++mt)
+      for (int v = 0; v < 5; ++v) acc[mt][v] = util_d4{0, 0, 0, 0};
+#pragma unroll 4
+    for (int st = 0; st < QS; ++st) {
+      const int q = 4 * st + g < NQ ? 4 * st + g : NQ - 1;  // past the rule: its weight is zero
+      const double rho = src[5 * q], u = src[5 * q + 1], v = src[5 * q + 2], w = src[5 * q + 3], p = src[5 * q + 4];
+      const double U[5] = {rho, rho * u, rho * v, rho * w, p / (gamma - 1.0) + 0.5 * rho * (u * u + v * v + w * w)};
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const double a = tab[(mt * QS + st) * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          if (kTail4 && mt == MT - 1)
+            acc[mt][c][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, U[c], acc[mt][c][0], 0, 0, 0);
+          else
+            acc[mt][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, U[c], acc[mt][c], 0, 0, 0);
+        }
+      }
+    }
+    // register j of lane group g: mode 16 mt + g + 4 j
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int c = 0; c < 5; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (4 * mt + j < NPQ)
+            out[(((int64_t)c * NPQ + 4 * mt + j) * m.epad + e) * 4 + g] =
+                16 * mt + 4 * j + g < NP ? S(acc[mt][c][j]) : S(0);
+  }
 }
 
 // Integrated slip-wall pressure J = sum_{wall faces} sum_q 2 A_f w^f_q p(U-_q) and dJ/dU,
@@ -189,31 +267,119 @@ __global__ __launch_bounds__(512) void stream_kernel(int kind, const stream_u4* 
   }
 }
 
+// Admissibility check: U at the volume quadrature points in fp64 (rows = points, k = modes, as the
+// stage kernel's interpolation) and one count per element where any value is not finite or the
+// density or pressure is not positive.  The count accumulates atomically into *n_bad, once per
+// workgroup.  (One thread per element read its coefficients again for every point.)
+template <int P, class S>
+__global__ __launch_bounds__(256) void check_state_kernel(MeshView m, RefView r, double gamma,
+                                                          const S* __restrict__ u,
+                                                          unsigned long long* __restrict__ n_bad) {
+  constexpr int NP = Ord<P>::NP, NQ = Ord<P>::NQ, QT = Ord<P>::QT, NPQ = npq_of(NP), KS = NPQ;
+  __shared__ double tab[QT * KS * 64];
+  __shared__ int count;
+  if (threadIdx.x == 0) count = 0;
+  for (int i = threadIdx.x; i < QT * KS * 64; i += 256) {
+    const int l = i % 64, st = i / 64 % KS, q = 16 * (i / 64 / KS) + l % 16, mode = 4 * st + l / 16;
+    tab[i] = q < NQ && mode < NP ? r.B[q * NP + mode] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int64_t ngroups = m.epad / 16, stride = (int64_t)gridDim.x * 4;
+  int found = 0;
+  for (int64_t grp = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); grp < ngroups; grp += stride) {
+    const int64_t e = grp * 16 + col;
+    double b[5][KS];
+#pragma unroll
+    for (int c = 0; c < 5; ++c)
+#pragma unroll
+      for (int st = 0; st < KS; ++st) {
+        const S x = u[(((int64_t)c * NPQ + st) * m.epad + e) * 4 + g];
+        b[c][st] = 4 * st + g < NP ? double(x) : 0.0;
+      }
+    bool bad = false;
+#pragma unroll 1
+    for (int qt = 0; qt < QT; ++qt) {
+      util_d4 d[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) d[c] = util_d4{0, 0, 0, 0};
+#pragma unroll
+      for (int st = 0; st < KS; ++st) {
+        const double a = tab[(qt * KS + st) * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) d[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c][st], d[c], 0, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double U[5] = {d[0][j], d[1][j], d[2][j], d[3][j], d[4][j]};
+        const double p = (gamma - 1.0) * (U[4] - 0.5 * (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) / U[0]);
+        bool finite = true;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) finite = finite && isfinite(U[c]);
+        if (16 * qt + g + 4 * j < NQ) bad = bad || !finite || !(U[0] > 0.0) || !(p > 0.0);
+      }
+    }
+    unsigned long long any = __ballot(bad && e < m.n_elem);  // lane groups of an element: bits col + 16 g
+    any |= any >> 32;
+    any |= any >> 16;
+    found += __popcll(any & 0xffffull);
+  }
+  if (lane == 0 && found) atomicAdd(&count, found);
+  __syncthreads();
+  if (threadIdx.x == 0 && count) atomicAdd(n_bad, (unsigned long long)count);
+}
+
+// Persistent column-tile launch: one wavefront per 16 elements, at most four workgroups per CU.
+unsigned tile_blocks(const MeshView& m) {
+  int dev = 0, ncu = 0;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t want = (m.epad / 16 + 3) / 4, fill = (int64_t)ncu * 4;
+  return (unsigned)(want < fill ? want : fill);
+}
+
 }  // namespace
 
+// Launch kernel<P, S> with S the mode's state type.
+#define TDG_BY_ORDER(KERNEL, GRID, ...)                                                              \
+  do {                                                                                               \
+    switch (p) {                                                                                     \
+      case 1: TDG_BY_STATE(KERNEL, 1, GRID, __VA_ARGS__); break;                                     \
+      case 2: TDG_BY_STATE(KERNEL, 2, GRID, __VA_ARGS__); break;                                     \
+      case 3: TDG_BY_STATE(KERNEL, 3, GRID, __VA_ARGS__); break;                                     \
+      case 4: TDG_BY_STATE(KERNEL, 4, GRID, __VA_ARGS__); break;                                     \
+      default: return hipErrorInvalidValue;                                                          \
+    }                                                                                                \
+    return hipGetLastError();                                                                        \
+  } while (0)
+#define TDG_BY_STATE(KERNEL, PP, GRID, ...)                                                          \
+  do {                                                                                               \
+    if (prec == 1) {                                                                                 \
+      using S = float;                                                                               \
+      hipLaunchKernelGGL((KERNEL<PP, S>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);                 \
+    } else {                                                                                         \
+      using S = double;                                                                              \
+      hipLaunchKernelGGL((KERNEL<PP, S>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);                 \
+    }                                                                                                \
+  } while (0)
+
 hipError_t launch_set_state(int p, int prec, const MeshView& m, const double* user, void* internal, hipStream_t s) {
-  if (prec == 1)
-    hipLaunchKernelGGL(set_state_kernel<float>, dim3(nblocks(m.epad, 256)), dim3(256), 0, s, m, np_of(p), user,
-                       (float*)internal);
-  else
-    hipLaunchKernelGGL(set_state_kernel<double>, dim3(nblocks(m.epad, 256)), dim3(256), 0, s, m, np_of(p), user,
-                       (double*)internal);
-  return hipGetLastError();
+  TDG_BY_ORDER(set_state_kernel, nblocks(m.epad, kTileE), m, user, (S*)internal);
 }
 
 hipError_t launch_get_state(int p, int prec, const MeshView& m, const void* internal, double* user, hipStream_t s) {
-  if (prec == 1)
-    hipLaunchKernelGGL(get_state_kernel<float>, dim3(nblocks(m.n_elem, 256)), dim3(256), 0, s, m, np_of(p),
-                       (const float*)internal, user);
-  else
-    hipLaunchKernelGGL(get_state_kernel<double>, dim3(nblocks(m.n_elem, 256)), dim3(256), 0, s, m, np_of(p),
-                       (const double*)internal, user);
-  return hipGetLastError();
+  TDG_BY_ORDER(get_state_kernel, nblocks(m.epad, kTileE), m, (const S*)internal, user);
 }
 
 hipError_t launch_volume_points(int p, const MeshView& m, const RefView& r, double* xyz, hipStream_t s) {
-  const int nq = (p + 1) * (p + 1) * (p + 1);
-  hipLaunchKernelGGL(volume_points_kernel, dim3(nblocks(m.n_elem * nq, 256)), dim3(256), 0, s, m, nq, r, xyz);
+  const dim3 grid(nblocks(m.n_elem, kTileE)), block(256);
+  switch (p) {
+    case 1: hipLaunchKernelGGL(volume_points_kernel<1>, grid, block, 0, s, m, r, xyz); break;
+    case 2: hipLaunchKernelGGL(volume_points_kernel<2>, grid, block, 0, s, m, r, xyz); break;
+    case 3: hipLaunchKernelGGL(volume_points_kernel<3>, grid, block, 0, s, m, r, xyz); break;
+    case 4: hipLaunchKernelGGL(volume_points_kernel<4>, grid, block, 0, s, m, r, xyz); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -230,40 +396,10 @@ hipError_t launch_wall_pressure(int p, int prec, const MeshView& m, const RefVie
   return hipGetLastError();
 }
 
-// Admissibility check: one thread per element evaluates U at the volume quadrature
-// points (fp64) and counts the element once if any value is not finite or the density or
-// pressure there is not positive.  The count accumulates atomically into *n_bad.
-template <class S>
-__global__ void check_state_kernel(MeshView m, int np, int nq, RefView r, double gamma, const S* __restrict__ u,
-                                   unsigned long long* __restrict__ n_bad) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m.n_elem) return;
-  bool bad = false;
-  for (int q = 0; q < nq && !bad; ++q) {
-    double U[5] = {0, 0, 0, 0, 0};
-    for (int i = 0; i < np; ++i) {
-      const double b = r.B[q * np + i];
-      for (int c = 0; c < 5; ++c) U[c] += b * double(u[sidx(c, i, e, m.epad, npq_of(np))]);
-    }
-    const double p = (gamma - 1.0) * (U[4] - 0.5 * (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) / U[0]);
-    bool finite = true;
-    for (int c = 0; c < 5; ++c) finite = finite && isfinite(U[c]);
-    bad = !finite || !(U[0] > 0.0) || !(p > 0.0);
-  }
-  if (bad) atomicAdd(n_bad, 1ULL);
-}
-
 hipError_t launch_check_state(int p, int prec, const MeshView& m, const RefView& r, double gamma, const void* u,
                               int64_t* n_bad, hipStream_t s) {
-  const int np = np_of(p), nq = (p + 1) * (p + 1) * (p + 1);
   hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(1), 0, s, (unsigned long long*)n_bad, 0ULL);
-  if (prec == 1)
-    hipLaunchKernelGGL(check_state_kernel<float>, dim3(nblocks(m.n_elem, 128)), dim3(128), 0, s, m, np, nq, r, gamma,
-                       (const float*)u, (unsigned long long*)n_bad);
-  else
-    hipLaunchKernelGGL(check_state_kernel<double>, dim3(nblocks(m.n_elem, 128)), dim3(128), 0, s, m, np, nq, r, gamma,
-                       (const double*)u, (unsigned long long*)n_bad);
-  return hipGetLastError();
+  TDG_BY_ORDER(check_state_kernel, tile_blocks(m), m, r, gamma, (const S*)u, (unsigned long long*)n_bad);
 }
 
 hipError_t launch_local_dt(int p, int prec, const MeshView& m, double gamma, double cfl, const void* u, double* dt,
@@ -277,15 +413,8 @@ hipError_t launch_local_dt(int p, int prec, const MeshView& m, double gamma, dou
 
 hipError_t launch_project(int p, int prec, const MeshView& m, const RefView& r, double gamma, const double* prim,
                           void* internal, hipStream_t s) {
-  const int np = np_of(p), nq = (p + 1) * (p + 1) * (p + 1);
   // padding elements map to caller element 0 (perm), so every row is a valid state
-  if (prec == 1)
-    hipLaunchKernelGGL(project_kernel<float>, dim3(nblocks(m.epad * np, 256)), dim3(256), 0, s, m, np, nq, r, gamma,
-                       prim, (float*)internal);
-  else
-    hipLaunchKernelGGL(project_kernel<double>, dim3(nblocks(m.epad * np, 256)), dim3(256), 0, s, m, np, nq, r, gamma,
-                       prim, (double*)internal);
-  return hipGetLastError();
+  TDG_BY_ORDER(project_kernel, tile_blocks(m), m, r, gamma, prim, (S*)internal);
 }
 
 hipError_t launch_stream_probe(int kind, const void* src, void* dst, size_t bytes, hipStream_t s) {
