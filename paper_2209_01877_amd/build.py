@@ -27,6 +27,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", os.path.
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
+    if src.endswith("_vgpr.hip"):  # MFMA results in ordinary registers
+        lang = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] + lang
     cmd = [HIPCC] + COMMON + lang + ["-c", src, "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

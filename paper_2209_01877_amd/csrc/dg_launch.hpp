@@ -85,6 +85,9 @@ struct RefView {
 };
 
 hipError_t launch_stage(int p, int prec, const StageArgs& a, hipStream_t stream);
+// Parts of launch_stage and launch_vjp in separately compiled files (*_vgpr.hip).
+hipError_t launch_stage_vgpr(int p, int prec, const StageArgs& a, hipStream_t stream);
+hipError_t launch_vjp_vgpr(const VjpArgs& a, hipStream_t stream);
 hipError_t launch_ns(int p, int prec, const ViscArgs& a, hipStream_t stream);
 hipError_t launch_ns_update(int p, int prec, const ViscArgs& a, hipStream_t stream);
 // Build the operand companion (q, c0) of an fp64 state for the mixed modes.

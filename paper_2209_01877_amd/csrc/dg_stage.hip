@@ -1091,6 +1091,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
   }
 }
 
+#ifndef TDG_VGPR_FORM
 // Operand companion of an fp64 state (mixed modes).  A workgroup packs 64 consecutive
 // elements (E_pad is a multiple of 64): the fp64 mode quads are read with the element
 // index fastest (contiguous 32-byte quads), converted into the records in LDS, and the
@@ -1166,6 +1167,7 @@ hipError_t launch_pack(int p, int prec, const MeshView& m, const void* u, void* 
 #undef TDG_PACK
   return hipErrorInvalidValue;
 }
+#endif
 
 template <int P, class Pr>
 static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
@@ -1215,23 +1217,36 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Instantiations that are faster with the MFMA results in ordinary registers (compiled in
+// dg_stage_vgpr.hip; us per stage at 44^3 x 6 elements, without and with): FP64 P3 1229 -> 1189,
+// mixed P4 1091 -> 1056.  FP64 P4 went from 5404 to 6062, the others changed by less than 2 %.
+constexpr bool vgpr_form(int p, int prec) { return (p == 3 && prec == 0) || (p == 4 && prec >= 2); }
+
+#ifdef TDG_VGPR_FORM
+hipError_t launch_stage_vgpr(int p, int prec, const StageArgs& a, hipStream_t stream) {
+  if (p == 3) return launch_stage_impl<3, PrecF64>(a, stream);
+  return prec == 2 ? launch_stage_impl<4, PrecBF16>(a, stream) : launch_stage_impl<4, PrecF16>(a, stream);
+}
+#else
 hipError_t launch_stage(int p, int prec, const StageArgs& a, hipStream_t stream) {
+  if (vgpr_form(p, prec)) return launch_stage_vgpr(p, prec, a, stream);
 #define TDG_CASE(PP, PR)                                                     \
   if (p == PP) return launch_stage_impl<PP, PR>(a, stream);
   switch (prec) {
     case 0:
-      TDG_CASE(1, PrecF64) TDG_CASE(2, PrecF64) TDG_CASE(3, PrecF64) TDG_CASE(4, PrecF64) break;
+      TDG_CASE(1, PrecF64) TDG_CASE(2, PrecF64) TDG_CASE(4, PrecF64) break;
     case 1:
       TDG_CASE(1, PrecF32) TDG_CASE(2, PrecF32) TDG_CASE(3, PrecF32) TDG_CASE(4, PrecF32) break;
     case 2:
-      TDG_CASE(1, PrecBF16) TDG_CASE(2, PrecBF16) TDG_CASE(3, PrecBF16) TDG_CASE(4, PrecBF16) break;
+      TDG_CASE(1, PrecBF16) TDG_CASE(2, PrecBF16) TDG_CASE(3, PrecBF16) break;
     case 3:
-      TDG_CASE(1, PrecF16) TDG_CASE(2, PrecF16) TDG_CASE(3, PrecF16) TDG_CASE(4, PrecF16) break;
+      TDG_CASE(1, PrecF16) TDG_CASE(2, PrecF16) TDG_CASE(3, PrecF16) break;
     default:
       break;
   }
 #undef TDG_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
 }  // namespace tetdg

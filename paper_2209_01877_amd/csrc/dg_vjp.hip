@@ -636,6 +636,14 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
   }
 }
 
+// Unsplit kernels that are faster with the MFMA results in ordinary registers (compiled in
+// dg_vjp_vgpr.hip): FP64 P2, at 32^3 x 6 elements 429 -> 417 us, with Roe's flux 751 -> 511 us.
+// The split kernel went from 15.6 to 17.7 us at 384 elements, the FP32 P3 kernel from 533 to 801.
+template <int P, class Pr>
+constexpr bool vjp_vgpr_form() {
+  return Pr::f64 && P == 2;
+}
+
 template <int P, class Pr, bool kRoe>
 hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
   int dev = 0, ncu = 0;
@@ -643,13 +651,20 @@ hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t ngroups = a.mesh.epad / 16;
   constexpr int limit = vjp_split_limit<P, Pr, kRoe>();
+#ifdef TDG_VGPR_FORM
+  constexpr bool kElsewhere = false;
+#else
+  constexpr bool kElsewhere = vjp_vgpr_form<P, Pr>();
   if (limit == kAlwaysSplit || (a.max_blocks == 0 && 2 * ngroups <= (int64_t)ncu * limit)) {
     // one group per workgroup, the same number of workgroups on every XCD
     hipLaunchKernelGGL((vjp_kernel<P, Pr, kRoe, false, 4>), dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(256), 0,
                        stream, a);
     return hipGetLastError();
   }
-  if constexpr (limit != kAlwaysSplit) {
+#endif
+  if constexpr (kElsewhere) {
+    return launch_vjp_vgpr(a, stream);
+  } else if constexpr (limit != kAlwaysSplit) {
     // tables in LDS when they fit in the share of one workgroup (160 KB per CU over the
     // workgroups resident per CU)
     constexpr bool lds = sizeof(typename Pr::Op) * VjpLayout<P>::n_slots * 64 <= 160 * 1024 / vjp_min_blocks<P, Pr>();
@@ -677,6 +692,9 @@ hipError_t launch_vjp_impl(const VjpArgs& a, hipStream_t stream) {
 
 }  // namespace
 
+#ifdef TDG_VGPR_FORM
+hipError_t launch_vjp_vgpr(const VjpArgs& a, hipStream_t stream) { return launch_vjp_impl<2, PrecF64>(a, stream); }
+#else
 hipError_t launch_vjp(int p, int prec, const VjpArgs& a, hipStream_t stream) {
   const bool f32 = prec == 1;  // the mixed modes keep an fp64 state: their adjoint is fp64
   switch (p) {
@@ -687,5 +705,6 @@ hipError_t launch_vjp(int p, int prec, const VjpArgs& a, hipStream_t stream) {
     default: return hipErrorInvalidValue;
   }
 }
+#endif
 
 }  // namespace tetdg
