@@ -226,6 +226,15 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
   const int64_t chunk = (ngroups + nx - 1) / nx;
   const int64_t g_begin = xcd * chunk;
   const int64_t g_end = g_begin + chunk < ngroups ? g_begin + chunk : ngroups;
+  // Wave priorities: the waves of a SIMD start together and, all else equal, stay in step, all of
+  // them in MFMAs, then in pointwise fluxes, then waiting for the epilogue's reads.  A priority that
+  // rises through the group (volume 1, faces 2 and 3, loads and epilogue 0) lets the one that is
+  // ahead finish its arithmetic first, so that its memory phase falls under the others' arithmetic.
+  // 48^3 x 6 elements, us per stage: fp16 P3 533 -> 497, FP32 P3 799 -> 746, P2 469 -> 441, P1 224 ->
+  // 192, FP64 P2 794 -> 752, P1 238 -> 225; no effect at one wave per SIMD.  The volume alone (537),
+  // one priority for volume and faces (529) or a fixed one per workgroup (549) gain less (fp16 P3).
+  // Split: the mixed modes alone gain (P3, 648 groups: 19.2 -> 18.4; FP64 P2 23.9 -> 24.6).
+  constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr>() >= 2;
   // a split wavefront's number: its first face and volume point tile, in strides of W
   const int wu = kSplit ? __builtin_amdgcn_readfirstlane(wslot) : 0;
 
@@ -313,6 +322,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc[mt][v] = Acc{0, 0, 0, 0};
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
     // ------------------------------------------------------------ volume integral
 #pragma unroll 1
     for (int qt = wu; qt < QT; qt += W) {
@@ -410,6 +420,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
       }
     }
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(2);
     // ------------------------------------------------------------ face integrals
     T fhs[9];  // split, mixed: the face's mean flux, normal and area
     if constexpr (Pr::mixed) {
@@ -454,6 +465,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
     }
 #pragma unroll 1
     for (int f = wu; f < 4; f += W) {
+      if (kPrio && !kSplit && f == 2) __builtin_amdgcn_s_setprio(3);
       T c0nn[5];
       T N[3];
       T nn;
@@ -598,6 +610,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
       (void)c0nn;
     }
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
     // ------------------------------------------------------------ split epilogue
     if constexpr (kSplit) {
       // (mode tile, variable) pairs 5 mt + v = wu (mod W): the state values are requested
