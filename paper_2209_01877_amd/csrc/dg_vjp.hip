@@ -292,7 +292,7 @@ constexpr int vjp_wave_bound() {
 // The split kernel runs up to this many 16-element groups per two CUs.  Times in us, unsplit |
 // split, at 24, 648, 1536 and 12288 groups (256 CUs), Rusanov:
 //   FP64  P1 20.0 19.5 34.3 172 | 8.4 14.0 25.3 167      P2 46.3 48.1 82.9 429 | 15.7 40.7 78.2 614
-//         P3 96.0 122 223 1395 | 26.7 71.9 140 1147      P4 458 701 1387 8940 | 140 566 1150 9187
+//         P3 96.0 122 223 1395 | 26.7 71.9 140 1147      P4 458 701 1387 7590 | 140 566 1150 9187
 //   FP32  P1 21.9 21.9 31.3 152 | 9.9 15.3 26.5 169      P2 35.1 35.6 54.1 254 | 12.8 24.2 42.8 276
 //         P3 56.3 64.4 109 531 | 20.0 45.5 82.1 566      P4 180 222 389 2194 | 61.3 193 372 2893
 // Where it is as fast at every size it is the only one: FP64 P1 and P3 (the unsplit P3 kernel
@@ -324,6 +324,10 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
   constexpr int NP = O::NP, NQ = O::NQ, NF = O::NF, MT = O::MT, QT = O::QT, FT = O::FT, KS = V::KS;
   static_assert(Pr::KW == 1, "the adjoint uses the f64/f32 instructions");
   constexpr bool kSplit = W > 1;
+  // rising wave priorities as in the stage kernel, for the two waves of a SIMD that sweep groups
+  // (FP32 at 32^3 x 6 elements, us: P1 152 -> 143, P2 249 -> 239, with Roe's flux 331 -> 308; the
+  // split kernels gain nothing)
+  constexpr bool kPrio = !kSplit && vjp_min_blocks<P, Pr>() == 2;
   // split: the element's own operands and, across the face, the volume part wait in LDS where that
   // makes two waves per SIMD fit (FP32 P4: one wave, the own operands alone); the FP64 kernels of
   // P2 and up would spill either way
@@ -424,6 +428,7 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc[mt][v] = Acc{0, 0, 0, 0};
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
     // ------------------------------------------------------------ volume
 #pragma unroll 1
     for (int qt = wu; qt < QT; qt += W) {
@@ -484,9 +489,11 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
         }
     }
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(2);
     // ------------------------------------------------------------ faces
 #pragma unroll 1
     for (int f = wu; f < 4; f += W) {
+      if (kPrio && f == 2) __builtin_amdgcn_s_setprio(3);
       T N[3];
       face_normal<T>(f, Md, N);
       const T nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
@@ -577,6 +584,7 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
     }
 
 
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
     if constexpr (kSplit) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
