@@ -138,9 +138,9 @@ int tdg_set_flux(tdg_ctx* ctx, int flux);
  * kappa = mu gamma / ((gamma - 1) Pr) and T = p / rho.  Every residual and RK entry point
  * then includes them (two launches per stage: the residual without the neighbours' viscous
  * face halves, and those halves with the stage's update).  Must be called before
- * tdg_mesh_upload (the device buffer then holds their scratch: one more state and each
- * element's own-side viscous face fluxes at its face points, 4 x 5 x 16 ceil(N_f / 16)
- * values).  FP64 and FP32 modes; the mixed
+ * tdg_mesh_upload (the device buffer then holds their scratch: one more state, in double in
+ * both modes, and each element's own-side viscous face fluxes at its face points,
+ * 4 x 5 x 16 ceil(N_f / 16) values).  FP64 and FP32 modes; the mixed
  * modes return TDG_ERR_UNSUPPORTED, and so do the adjoint entry points while mu > 0.
  * tdg_stable_dt stays the inviscid rule (the caller bounds dt by the viscous limit).
  * Errors: TDG_ERR_INVALID_ARG (mu < 0, Pr <= 0), TDG_ERR_STATE (mesh already uploaded). */

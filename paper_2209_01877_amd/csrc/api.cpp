@@ -486,9 +486,9 @@ int tdg_mesh_upload(tdg_ctx* c, int64_t n_elem, const int64_t* elem_vid, const d
     c->off_Bf = take(c->ref.Bf.size() * sizeof(double));
     // mixed modes: scratch operand companion for single residual / stage calls
     c->off_comp = take(c->prec >= TDG_MIXED_BF16 ? companion_bytes(c->p, epad) : 0);
-    // viscous scratch: the residual without the neighbours' viscous halves
+    // viscous scratch: the residual without the neighbours' viscous halves (double in every mode)
     {
-      const size_t sb = (size_t)5 * ((c->ref.np + 3) / 4) * epad * 4 * (c->prec == TDG_FP32 ? 4 : 8);
+      const size_t sb = (size_t)5 * ((c->ref.np + 3) / 4) * epad * 4 * sizeof(double);
       c->off_rv = take(c->mu > 0.0 ? sb : 0);
       // own-half viscous face fluxes at the face points (padded to whole 16-point tiles),
       // 4 faces x 5 variables per element

@@ -58,8 +58,8 @@ struct VjpArgs {
 };
 
 // Viscous (BR1) kernels: ns_kernel reads U and writes the residual without the neighbours' viscous
-// halves to out and the own halves to hbuf; ns_update_kernel reads both (r_own, hbuf) and writes R
-// or the stage update to out.  FP64 and FP32 (S = T = the mode's state type).
+// halves to out (double in both modes) and the own halves to hbuf; ns_update_kernel reads both (r_own,
+// hbuf) and writes R or the stage update to out.  FP64 and FP32 (S = T = the mode's state type).
 struct ViscArgs {
   const void* u;      // internal state read (and whose neighbours are read)
   const void* r_own;  // ns_update_kernel: ns_kernel's result

@@ -20,6 +20,8 @@
 // owner.  Each kernel writes only its own elements' outputs: no atomics.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dg_kernels.hpp"
 #include "dg_launch.hpp"
 #include "dg_tile.hpp"
@@ -90,12 +92,12 @@ __device__ __forceinline__ void lift_point(const typename Pr::Op* __restrict__ t
 }
 
 // Sum the lane groups' shares of the short last tile (FP32, as in the stage kernel).
-template <class Pr>
-__device__ __forceinline__ typename Pr::Acc finish_tail(typename Pr::Acc t) {
+template <class Pr, class V>
+__device__ __forceinline__ V finish_tail(V t) {
   if constexpr (!Pr::f64) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float x = t[j];
+      auto x = t[j];
       x += __shfl_xor(x, 16);
       x += __shfl_xor(x, 32);
       t[j] = x;
@@ -125,9 +127,10 @@ __device__ __forceinline__ typename Pr::Acc finish_tail(typename Pr::Acc t) {
 // several groups were slower (P3 FP64 2308: the loop costs registers, 284 bytes per lane spilled).
 //
 // Waves per SIMD: FP64 P2 at two spills 344 bytes per lane and is still the faster one (1139
-// against 1279 us).
+// against 1279 us); FP32 P1 at three spills 12 (a step at 32^3 x 6 elements 14 % faster than at two).
 template <int P, class Pr>
 constexpr int ns_waves() {
+  if (P == 1 && !Pr::f64) return 3;
   return P <= (Pr::f64 ? 2 : 3) ? 2 : 1;
 }
 
@@ -142,6 +145,11 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
   constexpr int NP = O::NP, NQ = O::NQ, NF = O::NF, MT = O::MT, QT = O::QT, FT = O::FT, KS = L::KS;
   constexpr int NPQ = npq_of(NP), W = 4, NPAIR = MT * 5;
   constexpr bool kTail4 = NP - 16 * (MT - 1) <= 4;
+  // FP32 P1: the viscous part in sums of its own, and Z's combination of the D_d (below) in fp64 FMAs.
+  // With the differences of the fluxes in one sum the residual was up to 5 % further from 64 bits than
+  // with the separate kernels' sums (mu = 1e-6 .. 100); now 4 % closer to 0.5 % further.  From P2 on the
+  // four wavefronts' short sums outweigh the difference's rounding (16-33 % closer with one sum).
+  constexpr bool kTwoSums = !Pr::f64 && P == 1;
   // the wavefronts' accumulators of one reduction; Z's operands between the two passes
   constexpr size_t kRed = sizeof(Acc) * W * NPAIR * 64, kZ = sizeof(Op) * 15 * KS * 64;
   __shared__ __align__(32) char lds_raw[kRed > kZ ? kRed : kZ];
@@ -159,6 +167,9 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
   if (grp >= ngroups) return;
   const uint32_t quad_bytes = (uint32_t)(epad * 4 * sizeof(S));
   const uint32_t var_bytes = quad_bytes * NPQ;
+  // a quad plane of the fp64 output: in FP32 mode a variable of it may pass 4 GiB
+  using RQ = typename std::conditional<Pr::f64, uint32_t, size_t>::type;
+  const RQ r_quad = (RQ)(epad * 4 * sizeof(double));
   const char* __restrict__ ubase = reinterpret_cast<const char*>(a.u);
   S* __restrict__ hb = reinterpret_cast<S*>(a.hbuf);
   const T gamma = T(a.gamma), gm1 = T(a.gamma - 1.0);
@@ -177,10 +188,11 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
         red[(w * NPAIR + mt * 5 + v) * 64 + lane] = on ? x[mt][v] + y[mt][v] : x[mt][v];
     __syncthreads();
   };
+  typedef double d4_t __attribute__((ext_vector_type(4)));
   auto shared_sum = [&](int mt, int v) {
-    Acc t = red[(mt * 5 + v) * 64 + lane];
+    d4_t t = __builtin_convertvector(red[(mt * 5 + v) * 64 + lane], d4_t);
 #pragma unroll
-    for (int x = 1; x < W; ++x) t += red[(x * NPAIR + mt * 5 + v) * 64 + lane];
+    for (int x = 1; x < W; ++x) t += __builtin_convertvector(red[(x * NPAIR + mt * 5 + v) * 64 + lane], d4_t);
     return t;
   };
 
@@ -228,10 +240,11 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 
   Acc lift[MT][5];  // face w's share of D_(w-1) (face 0: of every D_d)
   Acc acc[MT][5];   // (V - S) - (Vv - Sv)
+  Acc accv[MT][5];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int v = 0; v < 5; ++v) lift[mt][v] = acc[mt][v] = Acc{0, 0, 0, 0};
+    for (int v = 0; v < 5; ++v) lift[mt][v] = acc[mt][v] = accv[mt][v] = Acc{0, 0, 0, 0};
   // up to P3 a wavefront has one tile of each kind and keeps the face's inviscid flux and the
   // volume points' U until pass 2; at P4 it lifts the flux at once and interpolates U again
   constexpr bool kKeep = P <= 3;
@@ -277,7 +290,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
           fi[j][v] = q < NF ? fi[j][v] : T(0);
         }
         lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, uh, lift);
-        if constexpr (!kKeep) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+        if constexpr (!kKeep || kTwoSums) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
       }
     }
   }
@@ -317,7 +330,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 5; ++v) D[mt][v] = Acc{0, 0, 0, 0};
+        for (int v = 0; v < 5; ++v) D[mt][v] = kTwoSums && on ? lift[mt][v] : Acc{0, 0, 0, 0};
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         if (w + W * t >= QT) continue;
@@ -330,18 +343,23 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
         }
       }
       if (dd > 0) __syncthreads();  // the previous direction's shares are read
-      share(D, lift, on);
+      share(D, lift, !kTwoSums && on);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int i = 0; i < NVW; ++i) {
           const int v = pair_v(mt, i);
           if (v >= 5) continue;
-          const Acc t = shared_sum(mt, v);
+          const d4_t t = shared_sum(mt, v);
 #pragma unroll
           for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) z[mt][i][k][j] = fmaT(Mt[3 * dd + k], T(t[j]), T(z[mt][i][k][j]));
+            for (int j = 0; j < 4; ++j) {
+              if constexpr (kTwoSums)
+                z[mt][i][k][j] = T(fma(Md[3 * dd + k], t[j], double(z[mt][i][k][j])));
+              else
+                z[mt][i][k][j] = fmaT(Mt[3 * dd + k], T(t[j]), T(z[mt][i][k][j]));
+            }
         }
     }
     __syncthreads();
@@ -354,8 +372,12 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
           T x[4];
+          if constexpr (kTail4)
+            if (mt == MT - 1) z[mt][i][k] = finish_tail<Pr>(z[mt][i][k]);
+          // |K| is fp64 in every mode: one product, rounded once (an fp32 1/|K| would scale all of Z
+          // by the same wrong factor)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) x[j] = -T(ivol) * T(z[mt][i][k][j]);
+          for (int j = 0; j < 4; ++j) x[j] = T(-ivol * double(z[mt][i][k][j]));
           Op* const zk = lz + (5 * k + v) * KS * 64;
           if constexpr (Pr::f64) {
             // register j of lane group g: mode 16 mt + g + 4 j, operand step 4 mt + j of this lane
@@ -363,12 +385,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
             for (int j = 0; j < 4; ++j)
               if (4 * mt + j < KS) zk[(4 * mt + j) * 64 + lane] = x[j];
           } else if (kTail4 && mt == MT - 1) {
-            // the lane groups' shares of modes 16 mt .. + 3: operand step 4 mt, mode 16 mt + g
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              x[j] += __shfl_xor(x[j], 16);
-              x[j] += __shfl_xor(x[j], 32);
-            }
+            // modes 16 mt .. + 3 in every lane group's registers: operand step 4 mt, mode 16 mt + g
             zk[4 * mt * 64 + lane] = g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : x[3];
           } else if (4 * mt + g < KS) {
             // register j of lane group g: mode 16 mt + 4 g + j, step 4 mt + g of lane group j
@@ -422,11 +439,14 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
       contra_flux<T>(U, Mt, gm1, yy);
 #pragma unroll
       for (int dd = 0; dd < 3; ++dd) {
-        T y[5];
+        T y[5], yv[5];
 #pragma unroll
-        for (int v = 0; v < 5; ++v)
-          y[v] = q < NQ ? yy[dd][v] - (Mt[3 * dd] * Fv[0][v] + Mt[3 * dd + 1] * Fv[1][v] + Mt[3 * dd + 2] * Fv[2][v])
-                        : T(0);
+        for (int v = 0; v < 5; ++v) {
+          yv[v] = Mt[3 * dd] * Fv[0][v] + Mt[3 * dd + 1] * Fv[1][v] + Mt[3 * dd + 2] * Fv[2][v];
+          y[v] = q < NQ ? (kTwoSums ? yy[dd][v] : yy[dd][v] - yv[v]) : T(0);
+          yv[v] = q < NQ ? -yv[v] : T(0);
+        }
+        if constexpr (kTwoSums) project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, yv, accv);
         project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, y, acc);
       }
     }
@@ -455,9 +475,9 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         h[v] = q < NF ? T(0.5) * h[v] : T(0);
-        fi[j][v] = kKeep ? fi[j][v] - h[v] : -h[v];
+        fi[j][v] = kKeep && !kTwoSums ? fi[j][v] - h[v] : -h[v];
       }
-      lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+      lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], kTwoSums ? accv : acc);
       // the own half of an interior face, for the neighbour's side of this face: per
       // (element, face, variable) 16 FT values, the point held in register j of lane
       // group g at 16 ft + 4 g + j, so that a reader's lane gets its four points at once
@@ -468,25 +488,35 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
     }
   }
 
-  // ---------------- the residual without the neighbours' halves
+  // ---------------- the residual without the neighbours' halves, in fp64 from here to the end of the
+  // update: the wavefronts' sums, 1/|K| and the store
   __syncthreads();
-  share(acc, acc, false);
+  d4_t own[kTwoSums ? NVW : 1];  // P1 (one mode tile): the inviscid part
+  if constexpr (kTwoSums) {
+    share(acc, acc, false);
+#pragma unroll
+    for (int i = 0; i < NVW; ++i)
+      if (pair_v(0, i) < 5) own[i] = shared_sum(0, pair_v(0, i));
+    __syncthreads();
+  }
+  share(kTwoSums ? accv : acc, acc, false);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int i = 0; i < NVW; ++i) {
       const int v = pair_v(mt, i);
       if (v >= 5) continue;
-      Acc t = shared_sum(mt, v);
+      d4_t t = shared_sum(mt, v);
+      if constexpr (kTwoSums) t += own[i];
       if (kTail4 && mt == MT - 1) t = finish_tail<Pr>(t);
       if (!live) continue;
-      char* const ob = reinterpret_cast<char*>(a.out) + (size_t)v * var_bytes + eoff;
+      char* const ob = reinterpret_cast<char*>(a.out) + (size_t)v * (r_quad * NPQ) + (RQ)e * 4 * sizeof(double);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int mode = 16 * mt + drow(Pr::f64, g, j);
         if ((mode >> 2) < NPQ)
-          *reinterpret_cast<S*>(ob + (uint32_t)(mode >> 2) * quad_bytes + (mode & 3) * sizeof(S)) =
-              S(mode < NP ? ivol * double(t[j]) : 0.0);
+          *reinterpret_cast<double*>(ob + (RQ)(mode >> 2) * r_quad + (mode & 3) * sizeof(double)) =
+              mode < NP ? ivol * t[j] : 0.0;
       }
     }
 }
@@ -568,7 +598,9 @@ __global__ __launch_bounds__(256) void ns_update_kernel(ViscArgs a) {
               const size_t o = (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
                                ((size_t)e * 4 + (mode & 3)) * sizeof(S);
               auto at = [&](const void* p) { return double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + o)); };
-              double r = at(a.r_own) + ivol * double(acc[mt][v][j]);
+              const double own =
+                  reinterpret_cast<const double*>(a.r_own)[((size_t)(v * NPQ + (mode >> 2)) * epad + e) * 4 + (mode & 3)];
+              double r = own + ivol * double(acc[mt][v][j]);
               if (a.rk) {
                 const double u0 = a.alpha != 0.0 ? at(a.u0) : 0.0;
                 r = a.alpha * u0 + (1.0 - a.alpha) * (at(a.u) + dt * r);
