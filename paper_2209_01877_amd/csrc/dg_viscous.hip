@@ -585,30 +585,30 @@ __global__ __launch_bounds__(256) void ns_update_kernel(ViscArgs a) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc[MT - 1][v] = finish_tail<Pr>(acc[MT - 1][v]);
     }
-    if (e < mv.n_elem) {
-      const double ivol = mv.inv_vol[e];
+    // the padding's elements get zeros (a caller may reduce over the padded array)
+    const bool live = e < mv.n_elem;
+    const double ivol = mv.inv_vol[e];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 5; ++v)
+      for (int v = 0; v < 5; ++v)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int mode = 16 * mt + drow(Pr::f64, g, j);
-            if ((mode >> 2) < NPQ) {
-              const size_t o = (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
-                               ((size_t)e * 4 + (mode & 3)) * sizeof(S);
-              auto at = [&](const void* p) { return double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + o)); };
-              const double own =
-                  reinterpret_cast<const double*>(a.r_own)[((size_t)(v * NPQ + (mode >> 2)) * epad + e) * 4 + (mode & 3)];
-              double r = own + ivol * double(acc[mt][v][j]);
-              if (a.rk) {
-                const double u0 = a.alpha != 0.0 ? at(a.u0) : 0.0;
-                r = a.alpha * u0 + (1.0 - a.alpha) * (at(a.u) + dt * r);
-              }
-              *reinterpret_cast<S*>(reinterpret_cast<char*>(a.out) + o) = S(mode < NP ? r : 0.0);
+        for (int j = 0; j < 4; ++j) {
+          const int mode = 16 * mt + drow(Pr::f64, g, j);
+          if ((mode >> 2) < NPQ) {
+            const size_t o = (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
+                             ((size_t)e * 4 + (mode & 3)) * sizeof(S);
+            auto at = [&](const void* p) { return double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + o)); };
+            const double own =
+                reinterpret_cast<const double*>(a.r_own)[((size_t)(v * NPQ + (mode >> 2)) * epad + e) * 4 + (mode & 3)];
+            double r = own + ivol * double(acc[mt][v][j]);
+            if (a.rk) {
+              const double u0 = a.alpha != 0.0 ? at(a.u0) : 0.0;
+              r = a.alpha * u0 + (1.0 - a.alpha) * (at(a.u) + dt * r);
             }
+            *reinterpret_cast<S*>(reinterpret_cast<char*>(a.out) + o) = S(mode < NP && live ? r : 0.0);
           }
-    }
+        }
   }
 }
 
