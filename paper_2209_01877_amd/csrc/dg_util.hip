@@ -112,7 +112,8 @@ __global__ __launch_bounds__(256) void project_kernel(MeshView m, RefView r, dou
       for (int v = 0; v < 5; ++v) acc[mt][v] = util_d4{0, 0, 0, 0};
 #pragma unroll 4
     for (int st = 0; st < QS; ++st) {
-      const int q = 4 * st + g < NQ ? 4 * st + g : NQ - 1;  // past the rule: its weight is zero
+      const bool in = 4 * st + g < NQ;
+      const int q = in ? 4 * st + g : NQ - 1;
       const double rho = src[5 * q], u = src[5 * q + 1], v = src[5 * q + 2], w = src[5 * q + 3], p = src[5 * q + 4];
       const double U[5] = {rho, rho * u, rho * v, rho * w, p / (gamma - 1.0) + 0.5 * rho * (u * u + v * v + w * w)};
 #pragma unroll
@@ -120,10 +121,11 @@ __global__ __launch_bounds__(256) void project_kernel(MeshView m, RefView r, dou
         const double a = tab[(mt * QS + st) * 64 + lane];
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
+          const double b = in ? U[c] : 0.0;  // past the rule: an infinity times a zero weight would be NaN
           if (kTail4 && mt == MT - 1)
-            acc[mt][c][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, U[c], acc[mt][c][0], 0, 0, 0);
+            acc[mt][c][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, acc[mt][c][0], 0, 0, 0);
           else
-            acc[mt][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, U[c], acc[mt][c], 0, 0, 0);
+            acc[mt][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[mt][c], 0, 0, 0);
         }
       }
     }

@@ -1,10 +1,11 @@
-"""What the calls write into outputs that hold garbage (NaN) before."""
+"""What the calls write into outputs that hold garbage (NaN) before, and of infinite inputs."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
 from gpu_common import make_mesh, oracle, random_state, solver  # noqa: E402
+from paper_2209_01877_amd import debug_tables  # noqa: E402
 
 
 def unused_modes(s, X):
@@ -28,3 +29,27 @@ def test_viscous_padding_is_written_as_zeros(p, prec):
         assert torch.isfinite(out[:, :, :s.n_elem]).all()
         assert not out[:, :, s.n_elem:].any()
         assert not unused_modes(s, out).any()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_projection_of_an_infinite_point(p, prec):
+    """An infinite pressure at one point makes every energy coefficient infinite, with the sign of
+    the mode at that point; the last point of the rule is where a padded contraction would
+    multiply it by a zero weight."""
+    mesh = make_mesh("ragged")
+    s = solver(p, prec, mesh)
+    NQ, NP = s.n_vol_points, s.n_modes
+    B = torch.from_numpy(debug_tables(p, 4).reshape(NQ, NP))
+    prim = torch.ones(mesh.n_elem, NQ, 5, dtype=torch.float64)
+    points = {3: NQ - 1, 5: 0}
+    for e, q in points.items():
+        prim[e, q, 4] = float("inf")
+    got = s.get_state(s.project(prim.cuda())).cpu()
+    s.sync()
+    for e, q in points.items():
+        assert (B[q] != 0).all()
+        assert torch.equal(got[e, 4], torch.sign(B[q]) * float("inf")), (q, got[e, 4])
+        assert torch.isfinite(got[e, :4]).all()
+    got[list(points), 4] = 0.0
+    assert torch.isfinite(got).all()
