@@ -20,6 +20,7 @@
 
 #include "dg_kernels.hpp"
 #include "dg_launch.hpp"
+#include "launch_rule.hpp"
 
 namespace tetdg {
 
@@ -681,13 +682,8 @@ hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
     hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
     if (err != hipSuccess) return err;
     if (per_cu < 1) per_cu = 1;
-    int64_t want = (ngroups + 3) / 4;
-    int64_t fill = (int64_t)ncu * per_cu;
-    int64_t nblk = want < fill ? want : fill;
+    int64_t nblk = sweep_blocks(ngroups, (int64_t)ncu * per_cu);
     if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-    // a multiple of 8 (one share per XCD), rounded up where the chip has room
-    if (nblk >= 8) nblk = nblk + 7 <= fill ? (nblk + 7) / 8 * 8 : nblk - nblk % 8;
-    if (nblk < 1) nblk = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
   }
   return hipGetLastError();
