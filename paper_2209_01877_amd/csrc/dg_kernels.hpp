@@ -13,6 +13,16 @@ typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 
+// Priority N of this wave among those of its SIMD, if `on` (uniform).  A branch of the compiler's around
+// s_setprio would cut the basic block, and with it the loads issued ahead (fp16 P3 stage 1-3 %
+// slower at every size).
+template <int N>
+__device__ __forceinline__ void wave_priority(int on) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_setprio %1\n1:" ::"s"(on), "n"(N) : "scc");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---------------------------------------------------------------- precision traits
 // S  : storage type of the state (global memory)
 // T  : arithmetic type of the pointwise fluxes

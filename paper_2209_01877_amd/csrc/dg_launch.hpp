@@ -14,7 +14,7 @@ struct StageArgs {
   double alpha, dt;   // U_out = alpha U0 + (1 - alpha)(U_in + dt R)
   const double* dt_dev;  // when non-null, dt is read from this device scalar instead
   int rk;             // 0: store R, 1: store the stage update
-  int max_blocks;     // 0: fill the device once
+  int prio;           // rising wave priorities (set by the launch, see rising_priority)
   MeshView mesh;
   const void* tab;    // packed MFMA operand tables
   const double* mom;       // mixed modes: [7][N_p] fp64 moments of the volume and face tables
@@ -49,7 +49,7 @@ struct VjpArgs {
   int n_terms;
   const void* y[3];
   double ya[3];
-  int max_blocks;
+  int prio;           // as in StageArgs
   MeshView mesh;
   const void* tab;    // packed VJP operand tables (f64 or f32)
   double gamma;

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc[mt][v] = Acc{0, 0, 0, 0};
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
+    if constexpr (kPrio) wave_priority<1>(a.prio);
     // ------------------------------------------------------------ volume integral
 #pragma unroll 1
     for (int qt = wu; qt < QT; qt += W) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
       }
     }
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(2);
+    if constexpr (kPrio) wave_priority<2>(a.prio);
     // ------------------------------------------------------------ face integrals
     T fhs[9];  // split, mixed: the face's mean flux, normal and area
     if constexpr (Pr::mixed) {
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
     }
 #pragma unroll 1
     for (int f = wu; f < 4; f += W) {
-      if (kPrio && !kSplit && f == 2) __builtin_amdgcn_s_setprio(3);
+      if (kPrio && !kSplit && f == 2) wave_priority<3>(a.prio);
       T c0nn[5];
       T N[3];
       T nn;
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
       (void)c0nn;
     }
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
+    if constexpr (kPrio) wave_priority<0>(a.prio);
     // ------------------------------------------------------------ split epilogue
     if constexpr (kSplit) {
       // (mode tile, variable) pairs 5 mt + v = wu (mod W): the state values are requested
@@ -1197,11 +1197,13 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t ngroups = a.mesh.epad / 16;
-  if (a.max_blocks == 0 && 2 * ngroups <= (int64_t)ncu * split_limit<P, Pr>()) {
+  StageArgs b = a;
+  b.prio = 1;
+  if (2 * ngroups <= (int64_t)ncu * split_limit<P, Pr>()) {
     auto kern = a.flux == 1 ? stage_kernel<P, Pr, false, true, kEpiRK, kSplitWaves>
                             : stage_kernel<P, Pr, false, false, kEpiRK, kSplitWaves>;
     // one group per workgroup, the same number of workgroups on every XCD
-    hipLaunchKernelGGL(kern, dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(64 * kSplitWaves), 0, stream, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(64 * kSplitWaves), 0, stream, b);
     return hipGetLastError();
   }
   auto kern = a.flux == 1 ? stage_kernel<P, Pr, lds, true, kEpiRK> : stage_kernel<P, Pr, lds, false, kEpiRK>;
@@ -1219,9 +1221,11 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
   if (err != hipSuccess) return err;
   if (per_cu < 1) per_cu = 1;
-  int64_t nblk = sweep_blocks(ngroups, (int64_t)ncu * per_cu);
-  if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
+  const int64_t nblk = sweep_blocks(ngroups, (int64_t)ncu * per_cu);
+  b.prio = rising_priority(ngroups, nblk, per_cu, Pr::mixed ? 4 : 3);
+  // mixed P3 with Rusanov's flux: 1 % slower with them also from 1.5 to 2 rounds
+  if (Pr::mixed && P == 3 && a.flux != 1 && ngroups > 4 * nblk && ngroups < 8 * nblk) b.prio = 0;
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, b);
   return hipGetLastError();
 }
 

@@ -188,7 +188,6 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
         red[(w * NPAIR + mt * 5 + v) * 64 + lane] = on ? x[mt][v] + y[mt][v] : x[mt][v];
     __syncthreads();
   };
-  typedef double d4_t __attribute__((ext_vector_type(4)));
   auto shared_sum = [&](int mt, int v) {
     d4_t t = __builtin_convertvector(red[(mt * 5 + v) * 64 + lane], d4_t);
 #pragma unroll

@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc[mt][v] = Acc{0, 0, 0, 0};
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
+    if constexpr (kPrio) wave_priority<1>(a.prio);
     // ------------------------------------------------------------ volume
 #pragma unroll 1
     for (int qt = wu; qt < QT; qt += W) {
@@ -490,11 +490,11 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
         }
     }
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(2);
+    if constexpr (kPrio) wave_priority<2>(a.prio);
     // ------------------------------------------------------------ faces
 #pragma unroll 1
     for (int f = wu; f < 4; f += W) {
-      if (kPrio && f == 2) __builtin_amdgcn_s_setprio(3);
+      if (kPrio && f == 2) wave_priority<3>(a.prio);
       T N[3];
       face_normal<T>(f, Md, N);
       const T nn = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(256, (vjp_wave_bound<P, Pr, W>())) void vjp_kernel(
     }
 
 
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
+    if constexpr (kPrio) wave_priority<0>(a.prio);
     if constexpr (kSplit) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
@@ -664,7 +664,7 @@ hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
   constexpr bool kElsewhere = false;
 #else
   constexpr bool kElsewhere = vjp_vgpr_form<P, Pr>();
-  if (limit == kAlwaysSplit || (a.max_blocks == 0 && 2 * ngroups <= (int64_t)ncu * limit)) {
+  if (limit == kAlwaysSplit || 2 * ngroups <= (int64_t)ncu * limit) {
     // one group per workgroup, the same number of workgroups on every XCD
     hipLaunchKernelGGL((vjp_kernel<P, Pr, kRoe, false, 4>), dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(256), 0,
                        stream, a);
@@ -682,9 +682,10 @@ hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
     hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
     if (err != hipSuccess) return err;
     if (per_cu < 1) per_cu = 1;
-    int64_t nblk = sweep_blocks(ngroups, (int64_t)ncu * per_cu);
-    if (a.max_blocks > 0 && nblk > a.max_blocks) nblk = a.max_blocks;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, a);
+    const int64_t nblk = sweep_blocks(ngroups, (int64_t)ncu * per_cu);
+    VjpArgs b = a;
+    b.prio = rising_priority(ngroups, nblk, per_cu, 3);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), 0, stream, b);
   }
   return hipGetLastError();
 }
