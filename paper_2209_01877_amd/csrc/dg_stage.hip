@@ -53,21 +53,22 @@ struct LiftPair<Pr, true> {
   typedef E1 type __attribute__((ext_vector_type(2)));
 };
 
-// Workgroups per CU (waves per SIMD) the stage kernel is compiled for: three for FP32 at P1 and P2
-// (at most 168 registers; 48^3-sized meshes 5-10 % faster than at two: P2 387 -> 366 us, with
-// Roe's flux 493 -> 442 us at 44^3 x 6 elements), two (at most 256 registers) for FP32 at P3, the
-// mixed modes up to P3 and FP64 up to P2; FP64 at P3 (~400 registers) and every P4 kernel run one.
-template <int P, class Pr>
+// Workgroups per CU (waves per SIMD) the stage kernel is compiled for: three for FP32 at P1 and, with
+// Rusanov's flux, P2 (at most 168 registers; 48^3 x 6 elements, two against three waves, us a step: P2
+// 1253 -> 1205), two (at most 256 registers) for FP32 at P3 and at P2 with Roe's flux (three spill 64
+// bytes per lane: 1585 -> 1494 us there, but 106 -> 113 at 1920 groups), the mixed modes up to P3 and
+// FP64 up to P2; FP64 at P3 (~400 registers) and every P4 kernel run one.
+template <int P, class Pr, bool kRoe>
 constexpr int stage_min_blocks() {
-  if (P <= 2 && !Pr::f64 && !Pr::mixed) return 3;
+  if (P <= (kRoe ? 1 : 2) && !Pr::f64 && !Pr::mixed) return 3;
   return (P <= 3 && !Pr::f64) || (P <= 2 && Pr::f64) ? 2 : 1;
 }
 
 // Wavefronts per SIMD of the split kernel (W wavefronts per group, see below): mixed P3 at
 // three (166 registers, 50 KB of LDS per workgroup), the others as the unsplit kernel.
-template <int P, class Pr, int W>
+template <int P, class Pr, bool kRoe, int W>
 constexpr int wave_bound() {
-  return W > 1 && Pr::mixed && P == 3 ? 3 : stage_min_blocks<P, Pr>();
+  return W > 1 && Pr::mixed && P == 3 ? 3 : stage_min_blocks<P, Pr, kRoe>();
 }
 
 // Wavefronts that share a group in the split kernel: one per face, and one per volume point
@@ -131,7 +132,7 @@ __device__ __forceinline__ X* split_lds() {
 // longer at every size up to the limit but one (FP64 P3, 376 groups: 32.5 against 35.1 us),
 // eight gained at most 10 % below 256 groups (mixed modes) and lost above.
 template <int P, class Pr, bool kLds, bool kRoe, int kEpi, int W = 1>
-__global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) void stage_kernel(
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, kRoe, W>())) void stage_kernel(
     StageArgs a) {
   constexpr bool kSplit = W > 1;
   static_assert(W == 1 || W == 4, "a wavefront per face");
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
   // 192, FP64 P2 794 -> 752, P1 238 -> 225; no effect at one wave per SIMD.  The volume alone (537),
   // one priority for volume and faces (529) or a fixed one per workgroup (549) gain less (fp16 P3).
   // Split: the mixed modes alone gain (P3, 648 groups: 19.2 -> 18.4; FP64 P2 23.9 -> 24.6).
-  constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr>() >= 2;
+  constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr, kRoe>() >= 2;
   // a split wavefront's number: its first face and volume point tile, in strides of W
   const int wu = kSplit ? __builtin_amdgcn_readfirstlane(wslot) : 0;
 
@@ -297,7 +298,9 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
         }
         (void)cx;
       } else {
-        load_operands<Pr, NP, KS>(ubase, var_bytes, (uint32_t)en * 4 * sizeof(S), om, bx);
+        // the modes past N_p are masked where the operands are used: a select on a value just
+        // requested made the compiler wait for the loads one by one (P2)
+        load_operands<Pr, NP, KS, 5, kNbrLds>(ubase, var_bytes, (uint32_t)en * 4 * sizeof(S), om, bx);
       }
     };
     Op bn[5][KS];
@@ -527,7 +530,8 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, W>())) voi
 #pragma unroll
               for (int v = 0; v < 5; ++v) {
                 const Op bv = kNbrLds ? nslot[(v * KS + s) * 64] : bn[v][s];
-                dp[v] = Pr::mfma(av, mine ? bv : Op{}, dp[v]);
+                const bool use = mine && (Pr::mixed || kNbrLds || om.keep[s]);
+                dp[v] = Pr::mfma(av, use ? bv : Op{}, dp[v]);
               }
             }
           }
@@ -1192,7 +1196,7 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   constexpr size_t comp_bytes =
       Pr::mixed ? sizeof(typename Pr::Op) / 8 * 4 * 16 * (5 * 32 * L::KS + 8) + 2 * sizeof(float) * 7 * 4 * 64 : 0;
   constexpr size_t nbr_bytes = stage_nbr_lds<P, Pr>() ? sizeof(typename Pr::Op) * 4 * 5 * L::KS * 64 : 0;
-  constexpr bool lds = tab_bytes + comp_bytes + nbr_bytes <= 160 * 1024 / stage_min_blocks<P, Pr>();
+  constexpr bool lds = tab_bytes + comp_bytes + nbr_bytes <= 160 * 1024 / stage_min_blocks<P, Pr, false>();
   int dev = 0, ncu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);

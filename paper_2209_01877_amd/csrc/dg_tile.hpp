@@ -29,7 +29,8 @@ struct OperandMap {
   }
 };
 
-template <class Pr, int NP, int KS, int NV = 5>
+// kMask = false leaves the modes past N_p to the consumer's mask (om.keep).
+template <class Pr, int NP, int KS, int NV = 5, bool kMask = true>
 __device__ __forceinline__ void load_operands(const char* __restrict__ base, uint32_t var_bytes, uint32_t elem_off,
                                               const OperandMap<Pr, NP, KS>& om, typename Pr::Op (&b)[NV][KS]) {
   using S = typename Pr::S;
@@ -40,7 +41,7 @@ __device__ __forceinline__ void load_operands(const char* __restrict__ base, uin
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         const S x = *reinterpret_cast<const S*>(vb + om.off[s] + elem_off);
-        b[v][s] = om.keep[s] ? typename Pr::Op(x) : typename Pr::Op(0);
+        b[v][s] = !kMask || om.keep[s] ? typename Pr::Op(x) : typename Pr::Op(0);
       }
     } else {
 #pragma unroll
