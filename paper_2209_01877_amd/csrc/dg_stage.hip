@@ -75,22 +75,24 @@ constexpr int wave_bound() {
 // tile at P3.
 constexpr int kSplitWaves = 4;
 
-// The split kernel runs up to this many 16-element groups per two CUs; above, the unsplit
-// kernel's one group per wavefront fills the chip better.  Stage times in us, unsplit | split,
-// at 24, 648 and 1536 groups (256 CUs), Rusanov:
-//   FP64  P1 14.1 15.0 19.6 | 6.8 11.3 19.4      P2 30.0 31.8 48.1 | 11.1 23.3 40.1
-//         P3 51.3 58.0 97.9 | 18.7 52.4 101.7    P4 181 182 361    | 58.4 173 339
-//   FP32  P1 13.0 13.4 18.0 | 6.7 10.9 17.2      P2 21.7 22.5 32.2 | 9.2 17.8 29.2
-//         P3 33.1 36.8 56.4 | 13.5 28.8 51.1     P4 101 118 196    | 31.1 87.7 171
-//   fp16  P1 15.1 16.6 22.7 | 9.4 15.7 27.0      P2 16.2 18.1 26.3 | 9.7 16.5 28.5
-//         P3 18.2 22.4 33.8 | 10.1 18.6 32.6     P4 37.4 46.6 81.5 | 18.0 51.8 101
-// The line lies below the largest mesh that the unsplit kernel takes in one round of
-// wavefronts (two per SIMD: 2048 groups; one per SIMD, FP64 P3 and every P4: 1024), since its
-// time is flat up to there.
+// The split kernel runs up to this many 16-element groups per two CUs.  Stage times in us, unsplit |
+// split, at 24, 648 and 1536 groups (256 CUs), Rusanov:
+//   FP64  P1 13.5 13.4 17.6 | 6.0 10.0 16.0      P2 30.4 30.4 46.4 | 11.5 23.2 39.6
+//         P3 49.2 54.5 92.8 | 17.4 47.0 89.8     P4 184 181 351    | 58.2 190 368
+//   FP32  P1 13.3 13.1 16.8 | 6.7 10.6 16.2      P2 21.1 20.9 29.9 | 9.3 17.4 28.5
+//         P3 33.6 34.9 54.9 | 13.5 28.8 50.3     P4 99.2 115 190   | 31.4 87.9 171
+//   fp16  P1 15.7 16.3 21.7 | 9.3 17.8 30.1      P2 16.7 17.8 25.0 | 9.6 19.4 33.1
+//         P3 19.1 22.2 32.3 | 10.5 17.8 31.7     P4 37.9 44.7 80.3 | 18.1 52.5 103
+// Split times go in rounds of the workgroups that fit, unsplit ones are flat up to a round of
+// wavefronts, so a line is the end of a round up to which the split form is not the slower one: mixed
+// P1 and P2 512 groups (500: 16.3 | 12.3, 576: 16.3 | 17.8), FP64 P4 512, mixed P3 768 for a
+// residual, whose unsplit form reads and writes least (768: 23.6 | 22.0, 780: 23.6 | 27.3), and
+// 1536 for a stage, although 769 to 860 groups then lose up to 3 %.  FP64 P3, FP32 P4 and mixed P4
+// stop short of further rounds that the split form would win.
 template <int P, class Pr>
-constexpr int split_limit() {
-  if (Pr::mixed) return P == 3 ? 12 : P == 4 ? 4 : 5;
-  if (Pr::f64) return P <= 2 ? 12 : 5;
+constexpr int split_limit(bool residual) {
+  if (Pr::mixed) return P == 3 ? (residual ? 6 : 12) : 4;
+  if (Pr::f64) return P <= 2 ? 12 : P == 3 ? 5 : 4;
   return P <= 3 ? 12 : 6;
 }
 
@@ -1203,7 +1205,7 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   const int64_t ngroups = a.mesh.epad / 16;
   StageArgs b = a;
   b.prio = 1;
-  if (2 * ngroups <= (int64_t)ncu * split_limit<P, Pr>()) {
+  if (2 * ngroups <= (int64_t)ncu * split_limit<P, Pr>(!a.rk)) {
     auto kern = a.flux == 1 ? stage_kernel<P, Pr, false, true, kEpiRK, kSplitWaves>
                             : stage_kernel<P, Pr, false, false, kEpiRK, kSplitWaves>;
     // one group per workgroup, the same number of workgroups on every XCD

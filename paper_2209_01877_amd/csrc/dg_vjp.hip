@@ -292,19 +292,26 @@ constexpr int vjp_wave_bound() {
 
 // The split kernel runs up to this many 16-element groups per two CUs.  Times in us, unsplit |
 // split, at 24, 648, 1536 and 12288 groups (256 CUs), Rusanov:
-//   FP64  P1 20.0 19.5 34.3 172 | 8.4 14.0 25.3 167      P2 46.3 48.1 82.9 429 | 15.7 40.7 78.2 614
-//         P3 96.0 122 223 1395 | 26.7 71.9 140 1147      P4 458 701 1387 7590 | 140 566 1150 9187
-//   FP32  P1 21.9 21.9 31.3 152 | 9.9 15.3 26.5 169      P2 35.1 35.6 54.1 254 | 12.8 24.2 42.8 276
-//         P3 56.3 64.4 109 531 | 20.0 45.5 82.1 566      P4 180 222 389 2194 | 61.3 193 372 2893
-// Where it is as fast at every size it is the only one: FP64 P1 and P3 (the unsplit P3 kernel
-// spilled 192 bytes per lane) and, with Roe's flux, P3 and P4 (1704 -> 1282 and 9886 -> 9094 us at
-// 12288 groups).  Otherwise the line lies below the largest mesh that the unsplit kernel takes in
-// one round of wavefronts.
+//   FP64  P1 19.9 18.9 32.8 171 | 9.2 13.6 24.3 165      P2 45.4 42.7 78.6 411 | 15.6 39.4 77.7 601
+//         P3 96.1 101 187 1075 | 27.0 71.3 139 1097      P4 424 610 1178 7289 | 142 556 1134 8768
+//   FP32  P1 21.6 21.0 30.2 140 | 10.1 14.9 25.6 169     P2 34.9 33.1 49.5 235 | 13.3 23.1 40.0 269
+//         P3 58.1 57.7 106 525 | 20.1 42.6 78.7 561      P4 183 192 345 1742 | 59.6 163 332 2538
+// Every size is split for FP64 P1 and, with Roe's flux, P3 and P4 (P3 1422 | 1240 at 12288 groups;
+// of P4 the unsplit form of this source is 4-8 % faster from 1728 groups on, but not compiled).
+// FP64 P3 splits up to 10752 groups (9788 and 10296: 3-5 % faster, 12288 and more: 2-4 % slower).  Otherwise the line
+// lies below the largest mesh that the unsplit kernel takes in one round of wavefronts.
 constexpr int kAlwaysSplit = 1 << 30;
 template <int P, class Pr, bool kRoe>
 constexpr int vjp_split_limit() {
-  if (Pr::f64 && (P == 3 || (P == 1 && !kRoe) || (P == 4 && kRoe))) return kAlwaysSplit;
+  if (Pr::f64 && ((P == 3 && kRoe) || (P == 1 && !kRoe) || (P == 4 && kRoe))) return kAlwaysSplit;
+  if (Pr::f64 && P == 3) return 84;
   return (Pr::f64 && P == 2) || (!Pr::f64 && P == 4) ? 5 : 12;
+}
+// FP64 P4 (Rusanov): the split form, one workgroup per CU, needs a fourth round above 768 groups,
+// while the unsplit kernel ends its first at 1024 (780: 617 | 670, 1020: 628 | 757, 1056: 1009 | 855).
+template <int P, class Pr>
+constexpr bool vjp_unsplit_gap(int64_t ngroups, int64_t ncu) {
+  return Pr::f64 && P == 4 && ngroups > 3 * ncu && ngroups <= 4 * ncu;
 }
 
 // kRoe selects the face flux at compile time (Roe's adjoint needs more registers).  FP32 up
@@ -664,7 +671,7 @@ hipError_t launch_vjp_flux(const VjpArgs& a, hipStream_t stream) {
   constexpr bool kElsewhere = false;
 #else
   constexpr bool kElsewhere = vjp_vgpr_form<P, Pr>();
-  if (limit == kAlwaysSplit || 2 * ngroups <= (int64_t)ncu * limit) {
+  if (limit == kAlwaysSplit || (2 * ngroups <= (int64_t)ncu * limit && !vjp_unsplit_gap<P, Pr>(ngroups, ncu))) {
     // one group per workgroup, the same number of workgroups on every XCD
     hipLaunchKernelGGL((vjp_kernel<P, Pr, kRoe, false, 4>), dim3((unsigned)((ngroups + 7) / 8 * 8)), dim3(256), 0,
                        stream, a);
