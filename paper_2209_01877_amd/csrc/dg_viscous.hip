@@ -167,9 +167,10 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
   if (grp >= ngroups) return;
   const uint32_t quad_bytes = (uint32_t)(epad * 4 * sizeof(S));
   const uint32_t var_bytes = quad_bytes * NPQ;
-  // a quad plane of the fp64 output: in FP32 mode a variable of it may pass 4 GiB
+  // the fp64 output: in FP32 mode a variable of it may pass 4 GiB, in FP64 mode its offsets are the
+  // state's (written as such: other expressions for them cost 80 bytes per lane of spills at P2)
   using RQ = typename std::conditional<Pr::f64, uint32_t, size_t>::type;
-  const RQ r_quad = (RQ)(epad * 4 * sizeof(double));
+  const RQ r_quad = Pr::f64 ? (RQ)quad_bytes : (RQ)(epad * 4 * sizeof(double));
   const char* __restrict__ ubase = reinterpret_cast<const char*>(a.u);
   S* __restrict__ hb = reinterpret_cast<S*>(a.hbuf);
   const T gamma = T(a.gamma), gm1 = T(a.gamma - 1.0);
@@ -245,8 +246,12 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 #pragma unroll
     for (int v = 0; v < 5; ++v) lift[mt][v] = acc[mt][v] = accv[mt][v] = Acc{0, 0, 0, 0};
   // up to P3 a wavefront has one tile of each kind and keeps the face's inviscid flux and the
-  // volume points' U until pass 2; at P4 it lifts the flux at once and interpolates U again
+  // volume points' U until pass 2; at P4 it lifts the flux at once and interpolates U again.  FP64 P2
+  // with Roe's flux lifts it at once too: kept, the kernel spilled 476 bytes per lane instead of 220
+  // and was slower than four separate kernels (a step at 32^3 x 6 elements: 4169 us kept, 3590 lifted
+  // at once, 3650 in four kernels).
   constexpr bool kKeep = P <= 3;
+  constexpr bool kLiftAtOnce = !kKeep || kTwoSums || (kRoe && Pr::f64 && P == 2);
   T fi[4][5];
 
   // ---------------- pass 1: face w, Uhat = (U- + U+)/2 and the inviscid flux
@@ -289,7 +294,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
           fi[j][v] = q < NF ? fi[j][v] : T(0);
         }
         lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, uh, lift);
-        if constexpr (!kKeep || kTwoSums) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+        if constexpr (kLiftAtOnce) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
       }
     }
   }
@@ -474,7 +479,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         h[v] = q < NF ? T(0.5) * h[v] : T(0);
-        fi[j][v] = kKeep && !kTwoSums ? fi[j][v] - h[v] : -h[v];
+        fi[j][v] = kLiftAtOnce ? -h[v] : fi[j][v] - h[v];
       }
       lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], kTwoSums ? accv : acc);
       // the own half of an interior face, for the neighbour's side of this face: per
@@ -509,7 +514,8 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
       if constexpr (kTwoSums) t += own[i];
       if (kTail4 && mt == MT - 1) t = finish_tail<Pr>(t);
       if (!live) continue;
-      char* const ob = reinterpret_cast<char*>(a.out) + (size_t)v * (r_quad * NPQ) + (RQ)e * 4 * sizeof(double);
+      char* const ob = reinterpret_cast<char*>(a.out) + (size_t)v * (Pr::f64 ? (RQ)var_bytes : r_quad * NPQ) +
+                       (Pr::f64 ? (RQ)eoff : (RQ)e * 4 * sizeof(double));
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int mode = 16 * mt + drow(Pr::f64, g, j);
