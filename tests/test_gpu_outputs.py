@@ -2,6 +2,8 @@
 import pytest
 import torch
 
+from synthetic import fields
+
 pytestmark = pytest.mark.gpu
 
 from gpu_common import make_mesh, oracle, random_state, solver  # noqa: E402
@@ -29,6 +31,26 @@ def test_viscous_padding_is_written_as_zeros(p, prec):
         assert torch.isfinite(out[:, :, :s.n_elem]).all()
         assert not out[:, :, s.n_elem:].any()
         assert not unused_modes(s, out).any()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16", "fp16"])
+def test_states_and_residuals_are_written_whole(p, prec):
+    mesh = make_mesh("ragged")
+    s = solver(p, prec, mesh)
+    user = random_state(oracle(p, mesh), seed=72).cuda()
+    U = s.set_state(user, garbage(s))
+    x = s.volume_points()
+    P = s.project(fields.RandomSmooth(5)(x).contiguous(), garbage(s))
+    R = s.residual(U, garbage(s))
+    S = s.rk_stage(U, U, garbage(s), 0.75, 1e-3)
+    s.sync()
+    for X in (U, P, R, S):
+        assert torch.isfinite(X[:, :, :s.n_elem]).all()
+        assert not unused_modes(s, X).any()
+    # set_state and project fill the padding with a copy of the first element
+    for X in (U, P):
+        assert torch.equal(X[:, :, s.n_elem:], X[:, :, :1].expand_as(X[:, :, s.n_elem:]))
 
 
 @pytest.mark.parametrize("p", [1, 2, 3, 4])
