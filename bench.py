@@ -36,7 +36,9 @@ from synthetic import fields, kuhn_cube  # noqa: E402
 HBM_PEAK_GBS = 8000.0
 ALU_PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3}  # MI355X vector (fp64 = its MFMA rate)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stage_kernel_p3_64cube_traffic.json")
-KERNEL_SOURCES = ["dg_stage.hip", "dg_kernels.hpp", "dg_common.hpp", "dg_launch.hpp", "dg_tile.hpp"]
+# what decides the stage kernels' code: their sources, the launch rules and the compiler flags
+KERNEL_SOURCES = ["csrc/dg_stage.hip", "csrc/dg_stage_vgpr.hip", "csrc/dg_kernels.hpp", "csrc/dg_common.hpp",
+                  "csrc/dg_launch.hpp", "csrc/launch_rule.hpp", "csrc/dg_tile.hpp", "build.py"]
 
 
 def kernel_source_hash() -> str:
@@ -44,7 +46,7 @@ def kernel_source_hash() -> str:
 
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_2209_01877_amd", "csrc", f), "rb") as fh:
+        with open(os.path.join(ROOT, "paper_2209_01877_amd", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
