@@ -102,10 +102,11 @@ int tdg_sizes(const tdg_ctx* ctx, int* n_modes, int* n_vol_points, int* n_face_p
 /* Upload a tetrahedral mesh (host arrays, copied).  Builds the face adjacency by
  * matching sorted vertex-id triples, tags boundary faces, computes FP64 geometry and
  * renumbers the elements (the grid renumbering of Sec. III.B: RCM, or a space-filling
- * curve).  The renumbering runs once, before time stepping.  For the FP64 and FP32 modes
- * the RCM and curve orders are then refined inside windows of 256 elements by grouping
- * elements with equal neighbour face codes (fewer distinct face tables per 16-element
- * tile in the stage kernel); the mixed modes keep the plain order.
+ * curve).  The renumbering runs once, before time stepping.  For the FP64 and FP32 modes,
+ * and the mixed modes at order 4, the RCM order is then refined inside windows of 256
+ * elements, and the curve orders inside windows of 4096, by grouping elements with equal
+ * neighbour face codes (fewer distinct face tables per 16-element tile in the stage kernel);
+ * the mixed modes up to order 3 keep the plain order.
  *   elem_vid   host int64 [n_elem][4]   global vertex ids (on a torus: periodic ids)
  *   elem_xyz   host double [n_elem][4][3] vertex coordinates, per element, unwrapped
  *   bface_vid  host int64 [n_bface][3]  boundary faces (any vertex order), may be NULL if 0

@@ -1,6 +1,7 @@
 // Fused element-centric DG residual + SSP-RK3 stage kernel for gfx950.
 //
-// One wavefront owns 16 elements at a time (the 16 columns of a 16x16 MFMA tile).
+// One wavefront owns 16 elements at a time (the 16 columns of a 16x16 MFMA tile); on small meshes the
+// four wavefronts of a workgroup share them (the split form, split_limit).
 // Every contraction of the residual is a small dense matrix (reference table)
 // times the 16 elements' coefficient or point-value columns, one MFMA per k-step
 // and conserved variable:

@@ -70,7 +70,7 @@ __device__ __forceinline__ void visc_flux(const T U[5], const T Z[3][5], T gm1, 
 // One direction dd of one point j of the projection: acc[mt][v] += P(mt, qt, 4 dd + j) y[v].
 template <class Pr, int MT, bool kTail4, class L>
 __device__ __forceinline__ void project_dir(const typename Pr::Op* __restrict__ tab, int qt, int j, int dd, int lane,
-                                            int g, typename Pr::T (&y)[5], typename Pr::Acc (&acc)[MT][5]) {
+                                            typename Pr::T (&y)[5], typename Pr::Acc (&acc)[MT][5]) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const typename Pr::Op av = tab[L::proj(mt, qt, 4 * dd + j) * 64 + lane];
@@ -82,7 +82,7 @@ __device__ __forceinline__ void project_dir(const typename Pr::Op* __restrict__ 
 // One point lk of the lift of a face tile: acc[mt][v] += L(mt, f, ft, lk) h[v].
 template <class Pr, int MT, bool kTail4, class L>
 __device__ __forceinline__ void lift_point(const typename Pr::Op* __restrict__ tab, int f, int ft, int lk, int lane,
-                                           int g, typename Pr::T (&h)[5], typename Pr::Acc (&acc)[MT][5]) {
+                                           typename Pr::T (&h)[5], typename Pr::Acc (&acc)[MT][5]) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const typename Pr::Op av = tab[L::lift(mt, f, ft, lk) * 64 + lane];
@@ -293,8 +293,8 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
           uh[v] = q < NF ? sgn * (um[v] + up[v]) : T(0);
           fi[j][v] = q < NF ? fi[j][v] : T(0);
         }
-        lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, uh, lift);
-        if constexpr (kLiftAtOnce) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], acc);
+        lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, uh, lift);
+        if constexpr (kLiftAtOnce) lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, fi[j], acc);
       }
     }
   }
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
           T y[5];
 #pragma unroll
           for (int v = 0; v < 5; ++v) y[v] = T(du1[t][v][j]);
-          project_dir<Pr, MT, kTail4, L>(tab, w + W * t, j, dd, lane, g, y, D);
+          project_dir<Pr, MT, kTail4, L>(tab, w + W * t, j, dd, lane, y, D);
         }
       }
       if (dd > 0) __syncthreads();  // the previous direction's shares are read
@@ -450,8 +450,8 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
           y[v] = q < NQ ? (kTwoSums ? yy[dd][v] : yy[dd][v] - yv[v]) : T(0);
           yv[v] = q < NQ ? -yv[v] : T(0);
         }
-        if constexpr (kTwoSums) project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, yv, accv);
-        project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, g, y, acc);
+        if constexpr (kTwoSums) project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, yv, accv);
+        project_dir<Pr, MT, kTail4, L>(tab, qt, j, dd, lane, y, acc);
       }
     }
   }
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256, (ns_waves<P, Pr>())) void ns_kernel(ViscArgs a
         h[v] = q < NF ? T(0.5) * h[v] : T(0);
         fi[j][v] = kLiftAtOnce ? -h[v] : fi[j][v] - h[v];
       }
-      lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, g, fi[j], kTwoSums ? accv : acc);
+      lift_point<Pr, MT, kTail4, L>(tab, w, ft, j, lane, fi[j], kTwoSums ? accv : acc);
       // the own half of an interior face, for the neighbour's side of this face: per
       // (element, face, variable) 16 FT values, the point held in register j of lane
       // group g at 16 ft + 4 g + j, so that a reader's lane gets its four points at once
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(256) void ns_update_kernel(ViscArgs a) {
           for (int j = 0; j < 4; ++j) h[j][v] = nbf >= 0 ? T(x[j]) : T(0);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lift_point<Pr, MT, kTail4, L>(tab, f, ft, j, lane, g, h[j], acc);
+        for (int j = 0; j < 4; ++j) lift_point<Pr, MT, kTail4, L>(tab, f, ft, j, lane, h[j], acc);
       }
     }
     if constexpr (kTail4) {
