@@ -54,22 +54,26 @@ struct LiftPair<Pr, true> {
   typedef E1 type __attribute__((ext_vector_type(2)));
 };
 
-// Workgroups per CU (waves per SIMD) the stage kernel is compiled for: three for FP32 at P1 and, with
-// Rusanov's flux, P2 (at most 168 registers; 48^3 x 6 elements, two against three waves, us a step: P2
-// 1253 -> 1205), two (at most 256 registers) for FP32 at P3 and at P2 with Roe's flux (three spill 64
-// bytes per lane: 1585 -> 1494 us there, but 106 -> 113 at 1920 groups), the mixed modes up to P3 and
-// FP64 up to P2; FP64 at P3 (~400 registers) and every P4 kernel run one.
-template <int P, class Pr, bool kRoe>
+// Forms of the epilogue (see stage_kernel).
+enum : int { kEpiRK = 0, kEpiResid = 1, kEpiRK0 = 2, kEpiRKW = 3 };
+
+// Workgroups per CU (waves per SIMD) the stage kernel is compiled for: three for FP32 at P1 and P2 (at
+// most 168 registers; 48^3 x 6 elements, two against three waves, us a step: P2 1253 -> 1205) but for
+// P2's stages with Roe's flux, where three spill 64 bytes per lane (1585 -> 1494 us there, but 106 -> 113
+// at 1920 groups; the residual form, with less to read, gains 3 % and loses nothing); two (at most 256
+// registers) for those, FP32 at P3, the mixed modes up to P3 and FP64 up to P2; FP64 at P3 (~400
+// registers) and every P4 kernel run one.
+template <int P, class Pr, bool kRoe, int kEpi>
 constexpr int stage_min_blocks() {
-  if (P <= (kRoe ? 1 : 2) && !Pr::f64 && !Pr::mixed) return 3;
+  if (P <= (kRoe && kEpi != kEpiResid ? 1 : 2) && !Pr::f64 && !Pr::mixed) return 3;
   return (P <= 3 && !Pr::f64) || (P <= 2 && Pr::f64) ? 2 : 1;
 }
 
 // Wavefronts per SIMD of the split kernel (W wavefronts per group, see below): mixed P3 at
 // three (166 registers, 50 KB of LDS per workgroup), the others as the unsplit kernel.
-template <int P, class Pr, bool kRoe, int W>
+template <int P, class Pr, bool kRoe, int kEpi, int W>
 constexpr int wave_bound() {
-  return W > 1 && Pr::mixed && P == 3 ? 3 : stage_min_blocks<P, Pr, kRoe>();
+  return W > 1 && Pr::mixed && P == 3 ? 3 : stage_min_blocks<P, Pr, kRoe, kEpi>();
 }
 
 // Wavefronts that share a group in the split kernel: one per face, and one per volume point
@@ -104,6 +108,14 @@ constexpr bool stage_nbr_lds() {
   return Pr::f64 && P != 3;
 }
 
+// A workgroup's LDS array of a split kernel (a function of its own, so that the other
+// instantiations do not carry it).
+template <class X, int N, int Tag>
+__device__ __forceinline__ X* split_lds() {
+  __shared__ X a[N];
+  return a;
+}
+
 // kLds: reference tables staged in LDS; kRoe: Roe's interface flux instead of Rusanov's
 // (a compile-time choice keeps the other flux's code and registers out of the kernel).
 // kEpi, the epilogue's form (a compile-time choice, so that the epilogue's state reads sit
@@ -113,16 +125,6 @@ constexpr bool stage_nbr_lds() {
 // U0, or (mixed modes) the update that
 // stores alpha_w U0 + (1 - alpha_w) times the stage result and writes the result's fp64
 // cell means beside its companion.
-enum : int { kEpiRK = 0, kEpiResid = 1, kEpiRK0 = 2, kEpiRKW = 3 };
-
-// A workgroup's LDS array of a split kernel (a function of its own, so that the other
-// instantiations do not carry it).
-template <class X, int N, int Tag>
-__device__ __forceinline__ X* split_lds() {
-  __shared__ X a[N];
-  return a;
-}
-
 // W: wavefronts that share one 16-element group.  1: each wavefront sweeps groups of its own
 // (large meshes).  Otherwise the workgroup's W = 4 wavefronts split one group (small meshes,
 // split_limit): a mesh that leaves the chip idle is bound by the latency of one group through
@@ -135,7 +137,7 @@ __device__ __forceinline__ X* split_lds() {
 // longer at every size up to the limit but one (FP64 P3, 376 groups: 32.5 against 35.1 us),
 // eight gained at most 10 % below 256 groups (mixed modes) and lost above.
 template <int P, class Pr, bool kLds, bool kRoe, int kEpi, int W = 1>
-__global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, kRoe, W>())) void stage_kernel(
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, kRoe, kEpi, W>())) void stage_kernel(
     StageArgs a) {
   constexpr bool kSplit = W > 1;
   static_assert(W == 1 || W == 4, "a wavefront per face");
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, kRoe, W>()
   // 192, FP64 P2 794 -> 752, P1 238 -> 225; no effect at one wave per SIMD.  The volume alone (537),
   // one priority for volume and faces (529) or a fixed one per workgroup (549) gain less (fp16 P3).
   // Split: the mixed modes alone gain (P3, 648 groups: 19.2 -> 18.4; FP64 P2 23.9 -> 24.6).
-  constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr, kRoe>() >= 2;
+  constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr, kRoe, kEpi>() >= 2;
   // a split wavefront's number: its first face and volume point tile, in strides of W
   const int wu = kSplit ? __builtin_amdgcn_readfirstlane(wslot) : 0;
 
@@ -1199,7 +1201,7 @@ static hipError_t launch_stage_impl(const StageArgs& a, hipStream_t stream) {
   constexpr size_t comp_bytes =
       Pr::mixed ? sizeof(typename Pr::Op) / 8 * 4 * 16 * (5 * 32 * L::KS + 8) + 2 * sizeof(float) * 7 * 4 * 64 : 0;
   constexpr size_t nbr_bytes = stage_nbr_lds<P, Pr>() ? sizeof(typename Pr::Op) * 4 * 5 * L::KS * 64 : 0;
-  constexpr bool lds = tab_bytes + comp_bytes + nbr_bytes <= 160 * 1024 / stage_min_blocks<P, Pr, false>();
+  constexpr bool lds = tab_bytes + comp_bytes + nbr_bytes <= 160 * 1024 / stage_min_blocks<P, Pr, false, kEpiRK>();
   int dev = 0, ncu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
