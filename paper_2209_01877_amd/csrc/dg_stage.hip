@@ -239,7 +239,8 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, (wave_bound<P, Pr, kRoe, kEpi
   // ahead finish its arithmetic first, so that its memory phase falls under the others' arithmetic.
   // 48^3 x 6 elements, us per stage: fp16 P3 533 -> 497, FP32 P3 799 -> 746, P2 469 -> 441, P1 224 ->
   // 192, FP64 P2 794 -> 752, P1 238 -> 225; no effect at one wave per SIMD.  The volume alone (537),
-  // one priority for volume and faces (529) or a fixed one per workgroup (549) gain less (fp16 P3).
+  // one priority for volume and faces (529) or a fixed one per workgroup (549) gain less (fp16 P3).  The
+  // launch leaves them off where a partial round would lose by them (rising_priority).
   // Split: the mixed modes alone gain (P3, 648 groups: 19.2 -> 18.4; FP64 P2 23.9 -> 24.6).
   constexpr bool kPrio = kSplit ? Pr::mixed : stage_min_blocks<P, Pr, kRoe, kEpi>() >= 2;
   // a split wavefront's number: its first face and volume point tile, in strides of W

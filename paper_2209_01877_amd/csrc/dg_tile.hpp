@@ -60,9 +60,10 @@ __device__ __forceinline__ void load_operands(const char* __restrict__ base, uin
 // tile of at most 4 modes (kTail4) one of the blocked 4x4 forms, whose B operand is the same.
 // FP64, 4x4x4 in four blocks: block b holds columns 4 b .. 4 b + 3, the four rows are the tile's
 // modes and k runs over the lane groups' points, so accumulator register 0 of lane group r holds
-// mode r (what the 16x16 form would put there).  It takes 20 cycles and one accumulator where
-// four FMAs per variable on the lane group's own point took 32 cycles, four accumulators and a
-// sum over the lane groups: FP64 stage, 48^3 x 6 elements, P1 291 -> 241 us, P3 1665 -> 1602 us.
+// mode r (what the 16x16 form would put there).  It takes 20 cycles (the 16x16 form 64) and one
+// accumulator where four FMAs per variable on the lane group's own point took 34 in one wave, four
+// accumulators and a sum over the lane groups: FP64 stage, 48^3 x 6 elements, P1 291 -> 241 us, P3 1665
+// -> 1602 us.
 // FP32, 4x4x1 in sixteen blocks: each lane group accumulates its own points'
 // share of the modes in registers 0..3, summed over the lane groups at the end.
 template <class Pr, bool kTail4>

@@ -596,24 +596,49 @@ __global__ __launch_bounds__(256) void ns_update_kernel(ViscArgs a) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int v = 0; v < 5; ++v)
+      for (int v = 0; v < 5; ++v) {
+        const char* const ro = reinterpret_cast<const char*>(a.r_own) + (size_t)v * NPQ * epad * 4 * sizeof(double);
+        auto update = [&](double own, double x, double u, double u0) {
+          double r = own + ivol * x;
+          if (a.rk) r = a.alpha * u0 + (1.0 - a.alpha) * (u + dt * r);
+          return r;
+        };
+        if constexpr (Pr::f64) {
+          // register j of lane group g: position g of quad 4 mt + j
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int mode = 16 * mt + drow(Pr::f64, g, j);
-          if ((mode >> 2) < NPQ) {
-            const size_t o = (size_t)v * var_bytes + (uint32_t)(mode >> 2) * quad_bytes +
-                             ((size_t)e * 4 + (mode & 3)) * sizeof(S);
-            auto at = [&](const void* p) { return double(*reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + o)); };
-            const double own =
-                reinterpret_cast<const double*>(a.r_own)[((size_t)(v * NPQ + (mode >> 2)) * epad + e) * 4 + (mode & 3)];
-            double r = own + ivol * double(acc[mt][v][j]);
-            if (a.rk) {
-              const double u0 = a.alpha != 0.0 ? at(a.u0) : 0.0;
-              r = a.alpha * u0 + (1.0 - a.alpha) * (at(a.u) + dt * r);
+          for (int j = 0; j < 4; ++j) {
+            const int mode = 16 * mt + drow(true, g, j);
+            if ((mode >> 2) < NPQ) {
+              const size_t q = ((size_t)(mode >> 2) * epad + e) * 4 + (mode & 3);
+              auto at = [&](const void* p) {
+                return reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + (size_t)v * var_bytes)[q];
+              };
+              const double r = update(reinterpret_cast<const double*>(ro)[q], acc[mt][v][j], a.rk ? at(a.u) : 0.0,
+                                      a.rk && a.alpha != 0.0 ? at(a.u0) : 0.0);
+              reinterpret_cast<double*>(reinterpret_cast<char*>(a.out) + (size_t)v * var_bytes)[q] =
+                  mode < NP && live ? r : 0.0;
             }
-            *reinterpret_cast<S*>(reinterpret_cast<char*>(a.out) + o) = S(mode < NP && live ? r : 0.0);
           }
+        } else if (4 * mt + g < NPQ) {
+          // lane group g holds quad 4 mt + g whole: one vector access each (value by value, the kernel
+          // moved 2.7 TB/s)
+          typedef S s4_t __attribute__((ext_vector_type(4)));
+          const size_t q = (size_t)(4 * mt + g) * epad + e;
+          auto at = [&](const void* p) {
+            return reinterpret_cast<const s4_t*>(reinterpret_cast<const char*>(p) + (size_t)v * var_bytes)[q];
+          };
+          const d4_t own = reinterpret_cast<const d4_t*>(ro)[q];
+          s4_t u = {0, 0, 0, 0}, u0 = {0, 0, 0, 0}, o;
+          if (a.rk) u = at(a.u);
+          if (a.rk && a.alpha != 0.0) u0 = at(a.u0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const double r = update(own[j], double(acc[mt][v][j]), double(u[j]), double(u0[j]));
+            o[j] = S(16 * mt + 4 * g + j < NP && live ? r : 0.0);
+          }
+          reinterpret_cast<s4_t*>(reinterpret_cast<char*>(a.out) + (size_t)v * var_bytes)[q] = o;
         }
+      }
   }
 }
 
