@@ -118,13 +118,14 @@ __device__ __forceinline__ V finish_tail(V t) {
 //      the (mode tile, variable) pairs of Z are dealt out over the wavefronts, which leave them in
 //      LDS as MFMA operands: Z never reaches memory.
 //   2. Fluxes at the volume points and the element's own face points from U and Z (both in LDS).
-// Bound by latency at one or two waves per SIMD (P3 FP64: 64-cycle MFMAs fill a third of the
-// time).  Before, Z was written by one kernel (2.4 KB per element at P3 FP64) and read back for every
-// point tile by a second one, a third added the neighbours' halves and the stage kernel the inviscid
-// part.  Whole stage at 32^3 x 6 elements, before and now, us: FP64 P1 634 -> 551, P2 1170 -> 1139,
-// P3 2484 -> 1866, P4 12679 -> 10550; FP32 416 -> 392, 769 -> 661, 1389 -> 969, 5183 -> 3677; at
-// 384 elements FP64 P1 59 -> 21, P3 187 -> 51.  Tables staged in LDS and workgroups that sweep
-// several groups were slower (P3 FP64 2308: the loop costs registers, 284 bytes per lane spilled).
+// Bound by latency at one or two waves per SIMD (P3 FP64: MFMA 0.38, VALU 0.22 of the time, waves waiting
+// 0.23 of theirs).  Before, Z was written by one kernel (2.4 KB per element at P3 FP64) and read back for
+// every point tile by a second one, a third added the neighbours' halves and the stage kernel the
+// inviscid part.  Whole stage at 32^3 x 6 elements, before and now, us, Rusanov: FP64 P1 634 -> 543, P2
+// 1172 -> 1134, P3 2475 -> 1840, P4 12554 -> 10498; FP32 413 -> 381, 764 -> 642, 1381 -> 890, 5163 -> 3603;
+// at 384 elements FP64 P1 59 -> 21, P3 188 -> 49, FP32 P3 145 -> 35.  Tables staged in LDS and workgroups
+// that sweep several groups were slower (P3 FP64 2308: the loop costs registers, 284 bytes per lane
+// spilled).  FP64 P4 spills 1452 (Roe 1468) bytes per lane, the kernels before it 1252 and 212.
 //
 // Waves per SIMD: FP64 P2 at two spills 344 bytes per lane and is still the faster one (1139
 // against 1279 us); FP32 P1 at three spills 12 (a step at 32^3 x 6 elements 14 % faster than at two).
